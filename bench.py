@@ -157,17 +157,15 @@ def cpu_baseline(Q, K, V, cfg, budget_s: float, call_flops: float) -> dict:
 
 
 def attn_kernel_label(g) -> str:
-    """Which attention kernel the library launches for this blocking: for blocks of 5
-    row tiles (129..160 slots) the software-pipelined kernel at d = 128 when its
-    9-chunk ring and the kept list fit one CU's 160 KB of LDS, else the paired kernel
-    when its 8-chunk ring and the list fit; the single-member kernel otherwise."""
+    """Which attention kernel the library launches for this blocking: blocks of 5 row tiles
+    (129..160 slots) run the 8-wave walk as attn_sw_kernel (d = 128, at most 3824 blocks)
+    or attn_pp_kernel (d = 64, or at most 7928 blocks), everything else attn_kernel."""
     tiles = -(-g.bt * g.bh * g.bw // 32)
-    chunk = 2 * 32 * g.d * 2
-    if tiles == 5 and g.d == 128 and 9 * chunk + 256 * 4 + 64 + g.NB * 4 <= 160 * 1024:
+    if tiles == 5 and g.d == 128 and g.NB <= 3824:
         return "spade attn_sw_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
-    if tiles == 5 and 8 * chunk + 256 * 4 + 8 * 4 + g.NB * 4 <= 160 * 1024:
-        return "spade attn_pp_kernel (paired waves, bf16 MFMA 32x32x16)"
-    return "spade attn_kernel (bf16 MFMA 32x32x16)"
+    if tiles == 5 and (g.d == 64 or g.NB <= 7928):
+        return "spade attn_pp_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
+    return "spade attn_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
 
 
 def traffic_record(kernel_file: str, workload_name: str):

@@ -1,33 +1,13 @@
 // Flash block-sparse attention (paper Eq. (2), §3.3 optimisation (3)) on gfx950.
 //
-// One workgroup per query block (b, h, i). Three kernels share the data movement
-// and the math below:
-// - attn_sw_kernel, for blocks of 5 row tiles (129..160 slots) at d = 128: one
-//   software-pipelined wave per 32-row tile, the fifth tile split over the four
-//   DMA waves (see its comment);
-// - attn_pp_kernel, for 5-tile blocks otherwise (d = 64, or kept lists too long
-//   for the sw kernel's LDS): two waves per 32-row tile split the kept walk (even /
-//   odd chunks) and alternate matrix and vector phases between barriers, so each
-//   SIMD overlaps one wave's MFMAs with the other's softmax; the pair merges by
-//   log-sum-exp;
-// - attn_kernel for every other block size: wave w owns query slots 32w..32w+31;
-//   for most block sizes one more wave only issues the K/V loads.
-// Work items are dealt to the 8 XCDs so that all XCDs share one head at a time;
-// each XCD starts its rows of a head heaviest first (heavy_first).
-// The kept K/V blocks of row (b, h, i) are walked in ascending block order in
-// chunks of 32 key slots (only chunks that hold real keys).
+// One workgroup per query block (b, h, i); its kept K/V blocks are walked in list order
+// in chunks of 32 keys (attn_walk.h). Work items are dealt to the 8 XCDs so that all XCDs
+// share one head at a time; each XCD starts its rows of a head heaviest first
+// (heavy_first).
 //
-// Data movement: each chunk's K and V rows go straight from HBM into LDS with
-// 16-byte global_load_lds (no register staging), double-buffered so chunk c+1
-// is in flight while chunk c is computed. The loads are issued from inline asm:
-// the compiler then schedules every LDS read with exact lgkmcnt tracking instead
-// of draining the in-flight LDS-DMA load before each read (it cannot prove the
-// load targets the other buffer); completion is ordered by the explicit wait and
-// barrier at the end of each chunk. The work item's kept list is staged in LDS
-// once, so the walk over kept blocks issues no vector-memory reads. Rows are stored unpadded with the
-// 16-byte pieces XOR-swizzled per row, which keeps both LDS read patterns below
-// free of bank conflicts. Key slots past a block's real tokens re-read the
-// block's last real row (finite data; their logits are masked).
+// Data movement: each chunk's K and V rows go straight from HBM into LDS with 16-byte
+// global_load_lds (no register staging) into a small ring, issued ahead of their use;
+// completion is ordered by explicit waits and barriers.
 //
 // Math, transposed so every softmax statistic is per lane:
 //   S^T (32 keys x 32 queries) = K * Q^T        v_mfma_f32_32x32x16_bf16, d/16 steps;
@@ -41,10 +21,17 @@
 // raised (and O rescaled) when some row's max grows by more than 2^8, so most
 // chunks skip the 64-register rescale; row sums use bf16 dot2 on the same packed
 // P that feeds the MFMA.
+//
+// What bounds it: the chip's power. At 1.6-1.7 GHz (2.4 when idle) the matrix pipes of a
+// dense walk are busy about 60% of the cycles; a mix of just this step's MFMAs, vector
+// work and LDS reads, without any loads from memory, ran at 1.3 PFLOP/s on the same card,
+// the walk's padded rate is 1.05-1.1. Fewer instructions and LDS bytes per MFMA, and
+// chunks without padding, are therefore what helps.
 #include <climits>
 #include <mutex>
 #include <type_traits>
 
+#include "attn_walk.h"
 #include "spade_internal.h"
 
 // Scratch of the allocation-free raster attention call: the head ranking's keys
@@ -57,215 +44,6 @@ static __device__ __align__(256) unsigned char scratch[spade::kNoAllocScratchByt
 namespace spade {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(3))) char lds_char;
-typedef __attribute__((address_space(3))) int lds_int;
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-
-constexpr int kChunk = 32;          // key slots per chunk
-constexpr float kRescaleLog2 = 8.0f;  // lazy-rescale threshold (base-2 logits)
-
-template <int D>
-struct Tile {
-  static constexpr int NCH = D / 8;                 // 16-byte pieces per row
-  static constexpr int ROW_BYTES = D * 2;
-  static constexpr int TILE_BYTES = kChunk * ROW_BYTES;
-  static constexpr int RPI = 64 / NCH;              // rows per wave-wide 1 KB load
-  static constexpr int LOADS = kChunk / RPI;        // wave loads per tile
-  static constexpr int BUF_BYTES = 2 * TILE_BYTES;  // K tile then V tile
-};
-
-// swizzles: LDS piece c of tile row r holds global piece c ^ f(r)
-template <int D>
-__device__ __forceinline__ int swz_k(int r) { return r & (Tile<D>::NCH - 1); }
-// V: in a transposing read, lanes 0-15 take pieces 4t + {0,1} and lanes 16-31 pieces
-// 4t + {2,3} of rows 0-3; an XOR stride of 4 pieces (d = 128) keeps the two groups'
-// pieces disjoint, so 32 lanes hit 64 distinct banks (no LDS bank conflicts)
-template <int D>
-__device__ __forceinline__ int swz_v(int r) { return D >= 128 ? 4 * (r & 3) : 2 * (r & 3); }
-
-// Position in the kept-block walk: list entry jj, its block j and real-key count nj,
-// the chunk's first key slot c0, and block j's extent (raster addressing).
-struct Cursor {
-  int jj, j, nj, c0;
-  BlockExt e;
-};
-
-// Raster token of slot `slot` of a block of any extent (ragged edge blocks).
-__device__ __forceinline__ int64_t ext_token(const DevGeom& g, const BlockExt& e, int slot) {
-  return block_slot_token(g, e, __builtin_amdgcn_rcpf(float(e.ew)),
-                          __builtin_amdgcn_rcpf(float(e.eh)), slot);
-}
-
-// Raster token of a block's first slot.
-__device__ __forceinline__ int64_t block_origin(const DevGeom& g, const BlockExt& e) {
-  return (int64_t(e.t0) * g.Hs + e.y0) * g.Ws + e.x0;
-}
-
-// Raster addressing of slot s of the cursor's block, relative to `base`: full
-// blocks (every block away from the grid's far edges) share one slot -> token
-// offset table `rel` (LDS, built once per workgroup), so a load costs one LDS
-// read instead of the division-based map; ragged blocks take the map.
-struct RasterRows {
-  bool full;
-  int64_t base;  // head_row + block origin (full), head_row (ragged)
-};
-
-__device__ __forceinline__ RasterRows raster_rows(const DevGeom& g, const Cursor& c,
-                                                  int64_t head_row) {
-  const bool full = c.e.n == g.BS;
-  return {full, head_row + (full ? block_origin(g, c.e) : 0)};
-}
-
-__device__ __forceinline__ Cursor next_chunk(const DevGeom& g, const lds_int* list, int cnt,
-                                             Cursor c) {
-  c.c0 += kChunk;
-  while (c.c0 >= c.nj) {
-    ++c.jj;
-    if (c.jj >= cnt) {
-      c.nj = 0;
-      c.c0 = 0;
-      return c;
-    }
-    const int j = __builtin_amdgcn_readfirstlane(list[c.jj]);  // uniform: keep in SGPRs
-    if (j >= 0 && j < g.NB) {
-      c.j = j;
-      c.e = block_ext(g, j);
-      c.nj = c.e.n;
-      c.c0 = 0;
-    }
-  }
-  return c;
-}
-
-// Loads of one chunk without a loader wave: wave w issues loads w, w + W, ...
-// of the 2*LOADS (K tiles, then V). wave_rows gives each of them its row
-// relative to the chunk's base row (blocked: the block's first row; RASTER: the
-// head's first raster row, plus the block origin for full blocks); it is called
-// one chunk ahead, so its LDS table reads complete under the current chunk's math.
-template <int D, int W>
-struct WaveLoads {
-  static constexpr int NQ = (2 * Tile<D>::LOADS + W - 1) / W;  // loads per wave (at most)
-};
-
-template <int D, int W, bool RASTER>
-__device__ __forceinline__ void wave_rows(const DevGeom& g, const Cursor& c, const lds_int* rel,
-                                          int wave, int lane, int (&rows)[WaveLoads<D, W>::NQ]) {
-  using TL = Tile<D>;
-  const int last = c.nj - 1 - c.c0;  // last real key slot of the chunk
-  auto fill = [&](auto row_of) {
-#pragma unroll
-    for (int k = 0; k < WaveLoads<D, W>::NQ; ++k) {
-      const int qq = (wave + k * W) % TL::LOADS;
-      rows[k] = row_of(c.c0 + min(qq * TL::RPI + lane / TL::NCH, last));
-    }
-  };
-  if (!RASTER)
-    fill([](int s) { return s; });
-  else if (c.e.n == g.BS)
-    fill([&](int s) { return rel[s]; });
-  else
-    fill([&](int s) { return int(ext_token(g, c.e, s)); });
-}
-
-template <int D, int W, bool RASTER>
-__device__ __forceinline__ void load_chunk(const DevGeom& g, const char* kb, const char* vb,
-                                           int64_t head_row, const Cursor& c,
-                                           const int (&rows)[WaveLoads<D, W>::NQ], lds_char* buf,
-                                           int wave, int lane) {
-  using TL = Tile<D>;
-  const int64_t base = RASTER ? raster_rows(g, c, head_row).base
-                              : head_row + int64_t(c.j) * g.BS;
-  const int piece = lane % TL::NCH;
-#pragma unroll
-  for (int k = 0; k < WaveLoads<D, W>::NQ; ++k) {
-    const int q = wave + k * W;
-    if (q < 2 * TL::LOADS) {
-      const bool is_v = q >= TL::LOADS;
-      const int qq = is_v ? q - TL::LOADS : q;
-      const int r = qq * TL::RPI + lane / TL::NCH;  // tile row (key slot in chunk)
-      const int gp = piece ^ (is_v ? swz_v<D>(r) : swz_k<D>(r));
-      const char* src = (is_v ? vb : kb) + (base + rows[k]) * TL::ROW_BYTES + gp * 16;
-      const uint32_t dst =  // M0: LDS base of this wave-wide 1 KB load
-          uint32_t(reinterpret_cast<uintptr_t>(buf)) + (is_v ? TL::TILE_BYTES : 0) + qq * 1024;
-      asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(dst) : "memory");
-    }
-  }
-}
-
-// Loader-wave variant: one extra wave issues all 2*LOADS loads of a chunk, so
-// the compute waves never wait on load issue or address arithmetic. The chunk
-// base is uniform (an SGPR pair); each lane adds its 32-bit row/piece offset.
-// RASTER: the base is the head's first raster row (plus the block origin for
-// full blocks) and the offset carries the slot's raster token (the head's rows
-// span < 2^31 bytes, checked on the host); a lane's K and V rows are the same,
-// so each offset is computed once.
-template <int D>
-__device__ __forceinline__ void loader_issue(const char* kb, const char* vb, int64_t base_row,
-                                             const uint32_t (&row_off)[Tile<D>::LOADS],
-                                             uint32_t lds_buf, int lane);
-
-template <int D, bool RASTER>
-__device__ __forceinline__ void loader_chunk(const DevGeom& g, const char* kb, const char* vb,
-                                             int64_t head_row, const Cursor& c, const lds_int* rel,
-                                             uint32_t lds_buf, int lane) {
-  using TL = Tile<D>;
-  const int last = c.nj - 1 - c.c0;  // last real key slot of the chunk
-  uint32_t row_off[TL::LOADS];       // byte offset of this lane's row in load qq
-  int64_t base_row;
-  auto fill = [&](auto row_of) {
-#pragma unroll
-    for (int qq = 0; qq < TL::LOADS; ++qq)
-      row_off[qq] = uint32_t(row_of(min(qq * TL::RPI + lane / TL::NCH, last)) * TL::ROW_BYTES);
-  };
-  if (!RASTER) {
-    base_row = head_row + int64_t(c.j) * g.BS + c.c0;
-    fill([](int sr) { return sr; });
-  } else {
-    const RasterRows rr = raster_rows(g, c, head_row);
-    base_row = rr.base;
-    if (rr.full)
-      fill([&](int sr) { return rel[c.c0 + sr]; });
-    else
-      fill([&](int sr) { return int(ext_token(g, c.e, c.c0 + sr)); });
-  }
-  loader_issue<D>(kb, vb, base_row, row_off, lds_buf, lane);
-}
-
-// The 2*LOADS wave-wide DMA loads of one chunk: K and V rows at base_row + the lane's
-// row offsets (bytes), into the chunk's LDS buffer.
-template <int D>
-__device__ __forceinline__ void loader_issue(const char* kb, const char* vb, int64_t base_row,
-                                             const uint32_t (&row_off)[Tile<D>::LOADS],
-                                             uint32_t lds_buf, int lane) {
-  using TL = Tile<D>;
-  const char* kbase = kb + base_row * TL::ROW_BYTES;
-  const char* vbase = vb + base_row * TL::ROW_BYTES;
-#pragma unroll
-  for (int q = 0; q < 2 * TL::LOADS; ++q) {
-    const bool is_v = q >= TL::LOADS;
-    const int qq = is_v ? q - TL::LOADS : q;
-    const int r = qq * TL::RPI + lane / TL::NCH;  // tile row (key slot in chunk)
-    const int gp = (lane % TL::NCH) ^ (is_v ? swz_v<D>(r) : swz_k<D>(r));
-    const uint32_t off = row_off[qq] + uint32_t(gp * 16);
-    const uint32_t dst = lds_buf + (is_v ? TL::TILE_BYTES : 0) + qq * 1024;  // M0
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(is_v ? vbase : kbase),
-                 "{m0}"(dst)
-                 : "memory");
-  }
-}
-
-// W compute waves (32 query slots each), plus one loader wave when LD. The
-// workgroup shapes are chosen so that a CU holds 12 waves at three waves per
-// SIMD (<= 168 VGPRs): 4 compute waves without a loader (3 workgroups per CU),
-// 5 compute waves with one (2 workgroups of 6).
-// RASTER: q, k, v and o are raster [B,H,N,d] (and lse [B,H,N]); every row is
-// addressed through the blocking's slot -> token map, so no blocked copies exist.
 struct NoTable {};
 
 // The work item of a workgroup: its geometry, (batch, head) pair, query block i
@@ -361,12 +139,572 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
   return it;
 }
 
-// MULTI (raster only): one launch over heads with different blockings; the work
-// item picks its head, and with it the geometry and block lists, from `tab`.
-template <int D, int W, bool LD, bool RASTER, bool MULTI>
-__global__ void __launch_bounds__(64 * (W + LD))
-    __attribute__((amdgpu_waves_per_eu(W + LD >= 3 ? 3 : 2)))
-    attn_kernel(DevGeom g_arg, const uint4* __restrict__ qb, const char* __restrict__ kb,
+// Workgroups of W waves, wave w on query slots 32 w .. 32 w + 31 for the whole walk, two
+// waves per SIMD (three at d = 64, where a step needs at most 166 registers): 8 / W
+// workgroups share a CU, so barriers of one are filled by another. The waves issue the DMA
+// themselves, 1 / W of a chunk's loads each, from inside their steps.
+// Rings of two K and two V tiles: in step c, after the sync in slot SY, K(c + 1) and
+// V(c - 1) have been read by every wave (their reads are in slots <= NS / 2 - 1), so K(c +
+// 3) and V(c + 1) are issued into their place; they are waited for at the next sync, a
+// step later. Deeper rings were slower: at d = 128 the 4-tile kernel of 120-key blocks
+// 27.5 ms with four tiles each against 26.7, 256-slot blocks 3.6 against 3.1 ms, and
+// workgroups of one and two waves lose residency (64-token blocks of a small layer 0.57
+// against 0.45 ms).
+// Against one wave per tile without pipelining (three waves per SIMD, LDS read latency in
+// every step): 120-slot blocks of a 75600-token, 40-head layer 29.7 -> 26.7 ms, 128-slot
+// blocks 3.0 -> 2.6 ms, 256-slot blocks 3.6 -> 3.1 ms, at d = 64 128-slot blocks 3.1 ->
+// 2.7 ms.
+template <int D, int W>
+struct WalkLayout {
+  static constexpr int TILE = KvTile<D>::BYTES;
+  static constexpr int V_OFF = 2 * TILE;
+  static constexpr int TAB_OFF = 4 * TILE;
+  static constexpr int LIST_OFF = TAB_OFF + 4 * W * 32 * 4;
+  // kept-list entries staged at a time: few where LDS decides how many workgroups a CU holds
+  static constexpr int SEG = W <= 2 ? 256 : 1024;
+  static constexpr int BYTES = LIST_OFF + (SEG + 1) * 8;
+  static constexpr int P2 = W >= 8 ? 8 : W >= 4 ? 4 : W >= 2 ? 2 : 1;
+  static constexpr int PW = KvTile<D>::LOADS > P2 ? KvTile<D>::LOADS / P2 : 1;  // loads per tile, wave
+  static constexpr int LW = KvTile<D>::LOADS / PW;                              // waves that load
+  static constexpr int ROWS = PW > 1 ? 2 : 1;  // rows of a chunk whose offsets a lane needs
+};
+
+template <int D, int W, bool RASTER, bool STREAM>
+__device__ __forceinline__ void row_tile_walk(const Item& it, const uint4* __restrict__ qb,
+                                              const char* __restrict__ kb,
+                                              const char* __restrict__ vb, float scale_log2,
+                                              __bf16* __restrict__ ob, float* __restrict__ lse,
+                                              char* smem_raw) {
+  using KV = KvTile<D>;
+  using LY = WalkLayout<D, W>;
+  constexpr int NT = 64 * W;
+  lds_char* const lds = (lds_char*)smem_raw;
+  lds_int* const list = (lds_int*)(smem_raw + LY::LIST_OFF);
+
+  const DevGeom g = it.g;
+  const BlockExt e_i = block_ext(g, it.i);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q0 = wave * 32;
+  const bool rows_live = q0 < e_i.n;
+  const int64_t head_row = RASTER ? it.bh * g.N : it.bh * g.NB * int64_t(g.BS);
+  const int64_t first_row = head_row + int64_t(it.i) * g.BS;  // blocked layout
+  TileState<D> x;
+  load_q<D, RASTER>(g, e_i, qb, head_row, first_row, q0, x.qf);
+  clear_tile(x);
+  const int cnt = min(max(*it.cnt_src, 0), g.NB);
+  slot_tables<D, W, RASTER>(g, (lds_int*)(smem_raw + LY::TAB_OFF), tid, NT);
+
+  const FragAddr fr(lane);
+  // this wave's loads of a tile: wave * PW .. + PW - 1
+  const bool loads = wave < LY::LW;
+  const int first = wave * LY::PW;
+  const char* const kbase = kb + head_row * KV::ROW + (first >> 1) * 64;
+  const char* const vbase = vb + head_row * KV::ROW + (first >> 1) * 64;
+  const uint32_t lds_load = uint32_t(reinterpret_cast<uintptr_t>(lds)) + first * 1024;
+  const int lane_row = ((lane >> 2) + (LY::ROWS == 1 ? 16 * (wave & 1) : 0)) * 4;
+  const uint32_t kx = k_piece(lane), dvx = v_piece(lane) - k_piece(lane);
+
+  for (int seg = 0; seg < cnt; seg += LY::SEG) {
+    const int ns = min(cnt - seg, LY::SEG);
+    if (seg) __syncthreads();
+    const Staged st = stage_list<D, RASTER, STREAM>(g, it.list_src + seg, ns, list, tid, lane, NT);
+    const int n = st.chunks;
+    if (n == 0) continue;
+    WalkCursor<LY::TAB_OFF, W, STREAM> cur(list, ns, st.stream);
+    // a tile's loads of this wave, rows at byte offsets r (K pieces) of the head
+    auto issue_k = [&](const uint32_t (&r)[2], int slot) {
+      if (loads)
+#pragma unroll
+        for (int k = 0; k < LY::PW; ++k)
+          tile_dma(kbase, r[k & (LY::ROWS - 1)], lds_load + slot * LY::TILE, k);
+    };
+    auto issue_v = [&](const uint32_t (&r)[2], int slot) {
+      if (loads)
+#pragma unroll
+        for (int k = 0; k < LY::PW; ++k)
+          tile_dma(vbase, r[k & (LY::ROWS - 1)] + dvx, lds_load + LY::V_OFF + slot * LY::TILE, k);
+    };
+    // Past the walk's end the cursor stays on the last chunk: the loads repeat it into
+    // slots that are not read again, so the steps need no case for it.
+    int t[2];
+    uint32_t add[2];  // t + add: rows of the chunk the cursor is on
+    auto rows_of = [&](uint32_t (&r)[2]) {
+#pragma unroll
+      for (int k = 0; k < LY::ROWS; ++k) r[k] = uint32_t(t[k]) + add[k];
+    };
+    int kv[5];                     // real keys of chunks c .. c + 4
+    uint32_t r0[2], rA[2], rB[2], rC[2];  // rows of chunks c + 1, c + 2, c + 3 in step c
+    auto fetch = [&](int c) {
+      if (c < n) cur.advance(1);
+      kv[c] = cur.keys();
+      cur.template look_up<LY::ROWS>(lds, lane_row, kx, t, add);
+    };
+    __builtin_amdgcn_s_waitcnt(0);  // Q and list loads are done: only DMA is counted below
+    fetch(0);
+    rows_of(r0);
+    issue_k(r0, 0);
+    fetch(1);
+    rows_of(rA);
+    issue_k(rA, 1);
+    wait_loads<0>();
+    __syncthreads();
+    f32x16 sA, sB;
+    uint32_t pA[8], pB[8];
+    if (rows_live) start_walk<D>(x, sA, pA, pB, lds, fr.k, fr.k + LY::TILE);
+    // P of "chunk -1" is zero; its V slot must hold finite values
+    for (int e = tid; e < LY::TILE / 16; e += NT)
+      *(uint4*)(smem_raw + LY::V_OFF + LY::TILE + e * 16) = make_uint4(0, 0, 0, 0);
+    fetch(2);
+    rows_of(rB);
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __syncthreads();
+    issue_k(rB, 0);
+    issue_v(r0, 0);
+    fetch(3);
+
+    // step c, c of parity `par`
+    auto step = [&](int c, int par, f32x16& sc, f32x16& sn, uint32_t (&pp)[8], uint32_t (&pn)[8]) {
+      constexpr int SY = D == 128 ? 9 : 4;
+      auto mid = [&](int s) {
+        if (s == 1) {  // the rows of c + 3 were looked up in the previous step
+          rows_of(rC);
+          if (c + 4 < n) cur.advance(1);
+          kv[4] = cur.keys();
+        }
+        if (s == SY) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          wait_loads<0>();
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          issue_k(rC, 1 - par);
+          issue_v(rA, 1 - par);
+        }
+        if (s == (D == 128 ? 4 : 2)) cur.template look_up<LY::ROWS>(lds, lane_row, kx, t, add);
+      };
+      if (rows_live) {
+        walk_step<D, SY>(
+            x, sc, sn, pp, pn, c, kv[0], scale_log2, lds,
+            [&](int d) { return fr.k + (d == c ? par : 1 - par) * LY::TILE; },
+            [&](int d) { return fr.v + LY::V_OFF + (d == c ? par : 1 - par) * LY::TILE; }, mid);
+      } else {
+#pragma unroll
+        for (int s = 0; s < 2 * KV::KK; ++s) mid(s);
+      }
+#pragma unroll
+      for (int k = 0; k < LY::ROWS; ++k) {
+        rA[k] = rB[k];
+        rB[k] = rC[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) kv[k] = kv[k + 1];
+    };
+    int c = 0;
+    if (rows_live) {
+#pragma unroll 1
+      for (; c + 1 < n; c += 2) {
+        step(c, 0, sA, sB, pA, pB);
+        step(c + 1, 1, sB, sA, pB, pA);
+      }
+      if (c < n) {
+        step(c, 0, sA, sB, pA, pB);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pA[k] = pB[k];
+      }
+      finish_chunk<D>(x, pA, lds, fr.v + LY::V_OFF + ((n - 1) & 1) * LY::TILE);
+    } else {
+#pragma unroll 1
+      for (; c < n; ++c) step(c, c & 1, sA, sB, pA, pB);
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // the loads past the walk's end
+  }
+  store_tile<D, RASTER>(g, e_i, x, q0, head_row, first_row, ob, lse);
+}
+
+// Blocks of 5 row tiles (129 .. 160 slots): eight waves, two per SIMD (waves w and w + 4
+// share one), one workgroup per CU.
+// - wave X_s (s = 0..3) owns query tile s for the whole walk;
+// - wave Y_s issues the DMA of every fourth chunk (s, s + 4, ...) and computes tile 4 on
+//   those same chunks with its own online-softmax state; the four partial states of tile
+//   4 merge by log-sum-exp at the end in a fixed order. So every SIMD carries 1.25 tiles.
+// The waves meet at one barrier per window of four chunks: barrier B_v makes window v
+// visible. In step c an X wave reads K of c + 2 and V^T of c, so it passes B_v in step 4v -
+// 2; then K up to 4v - 1 and V up to 4v - 3 have been read, and Y issues window v + 1: 8 K
+// and 10 V tiles are the fewest for which nothing unread is overwritten.
+// Against waves that read K of c + 1 and V^T of c in their own step, with whole swizzled
+// rows and a 9-chunk ring: 57600-token, 24-head layer of 160-slot blocks 6.40 -> 5.59 ms,
+// 32760-token, 12-head layer of 144-slot blocks 1.22 -> 1.00 ms, d = 64 against the
+// paired kernel 2.23 -> 1.79 ms (two batches of 16 heads, 19890 tokens).
+template <int D>
+struct FiveTileLayout {
+  static constexpr int TILE = KvTile<D>::BYTES, T = 5;
+  static constexpr int KRING = 8, VRING = 10;
+  static constexpr int V_OFF = KRING * TILE;
+  static constexpr int TAB_OFF = V_OFF + VRING * TILE;
+  static constexpr int KV_OFF = TAB_OFF + 4 * T * 32 * 4;  // real keys of chunk c at c % 16
+  static constexpr int LIST_OFF = KV_OFF + 64;
+  static constexpr int SEG = 512;  // kept-list entries staged at a time
+  static constexpr int BYTES = LIST_OFF + (SEG + 1) * 8;
+  static constexpr int MERGE_FLOATS = D / 32 * 16 + 2;  // per lane: O, m, l
+  static_assert(BYTES <= 160 * 1024, "one CU's LDS");
+};
+
+template <int D, bool RASTER, bool MULTI>
+__device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __restrict__ qb,
+                                               const char* __restrict__ kb,
+                                               const char* __restrict__ vb, float scale_log2,
+                                               __bf16* __restrict__ ob, float* __restrict__ lse,
+                                               char* smem_raw) {
+  using KV = KvTile<D>;
+  using LY = FiveTileLayout<D>;
+  constexpr int NT = 512;
+  lds_char* const lds = (lds_char*)smem_raw;
+  lds_int* const kval = (lds_int*)(smem_raw + LY::KV_OFF);
+  lds_int* const list = (lds_int*)(smem_raw + LY::LIST_OFF);
+
+  const DevGeom g = it.g;
+  const BlockExt e_i = block_ext(g, it.i);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sidx = wave & 3;  // X: tile; Y: chunk residue mod 4
+  const int q0 = (wave >= 4 ? 4 : sidx) * 32;
+  const bool rows_live = q0 < e_i.n;
+  const int64_t head_row = RASTER ? it.bh * g.N : it.bh * g.NB * int64_t(g.BS);
+  const int64_t first_row = head_row + int64_t(it.i) * g.BS;  // blocked layout
+  const int cnt = min(max(*it.cnt_src, 0), g.NB);
+  slot_tables<D, LY::T, RASTER>(g, (lds_int*)(smem_raw + LY::TAB_OFF), tid, NT);
+  const FragAddr fr(lane);
+
+  if (wave < 4) {
+    // ---- X ----
+    TileState<D> x;
+    load_q<D, RASTER>(g, e_i, qb, head_row, first_row, q0, x.qf);
+    clear_tile(x);
+    for (int seg = 0; seg < cnt; seg += LY::SEG) {
+      const int ns = min(cnt - seg, LY::SEG);
+      if (seg) __syncthreads();
+      const int n = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, list, tid, lane, NT).chunks;
+      if (n == 0) continue;
+      // P of "chunk -1" is zero; its V slot must hold finite values
+      for (int e = tid; e < LY::TILE / 16; e += 256)
+        *(uint4*)(smem_raw + LY::V_OFF + (LY::VRING - 1) * LY::TILE + e * 16) =
+            make_uint4(0, 0, 0, 0);
+      __syncthreads();  // B_0
+      if (!rows_live) {  // no query rows here: only the barriers of the walk
+#pragma unroll 1
+        for (int v = 1; v <= (n + 1) / 4; ++v) __syncthreads();
+        continue;
+      }
+      f32x16 sA, sB;
+      uint32_t pA[8], pB[8];
+      start_walk<D>(x, sA, pA, pB, lds, fr.k, fr.k + LY::TILE);
+      // real keys of chunk c, read a step ahead and moved to a scalar register: a wait for
+      // it at the top of a step would also drain the fragment reads just issued
+      int kv = __builtin_amdgcn_readfirstlane(kval[0]);
+      int vs = LY::V_OFF, vs_prev = LY::V_OFF + (LY::VRING - 1) * LY::TILE;  // V(c), V(c - 1)
+      auto step = [&](int c, f32x16& sc, f32x16& sn, uint32_t (&pp)[8], uint32_t (&pn)[8]) {
+        constexpr int SY = D == 128 ? 8 : 4;
+        int kv_next = 0;
+        auto mid = [&](int s) {
+          if (s != SY) return;
+          if ((c & 3) == 2) {  // B_v, v = (c + 2) / 4
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+          }
+          kv_next = kval[(c + 1) & 15];
+        };
+        walk_step<D, SY>(
+            x, sc, sn, pp, pn, c, kv, scale_log2, lds,
+            [&](int d) { return fr.k + ((d + 2) & (LY::KRING - 1)) * LY::TILE; },
+            [&](int d) { return fr.v + (d == c ? vs : vs_prev); }, mid);
+        kv = __builtin_amdgcn_readfirstlane(kv_next);
+        vs_prev = vs;
+        vs = vs == LY::V_OFF + (LY::VRING - 1) * LY::TILE ? LY::V_OFF : vs + LY::TILE;
+      };
+      int c = 0;
+#pragma unroll 1
+      for (; c + 1 < n; c += 2) {
+        step(c, sA, sB, pA, pB);
+        step(c + 1, sB, sA, pB, pA);
+      }
+      if (c < n) {
+        step(c, sA, sB, pA, pB);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) pA[k] = pB[k];
+      }
+      finish_chunk<D>(x, pA, lds, fr.v + vs_prev);
+    }
+    __syncthreads();  // every walk is done (the merge overwrites the rings)
+    __syncthreads();
+    store_tile<D, RASTER>(g, e_i, x, q0, head_row, first_row, ob, lse);
+    return;
+  }
+
+  // ---- Y ----
+  TileState<D> x;
+  load_q<D, RASTER>(g, e_i, qb, head_row, first_row, q0, x.qf);
+  clear_tile(x);
+  const int lane_row = (lane >> 2) * 4;
+  const uint32_t kx = k_piece(lane), dvx = v_piece(lane) - k_piece(lane);
+  const char* const kbase = kb + head_row * KV::ROW;
+  const char* const vbase = vb + head_row * KV::ROW;
+  const uint32_t lds_u32 = uint32_t(reinterpret_cast<uintptr_t>(lds));
+  for (int seg = 0; seg < cnt; seg += LY::SEG) {
+    const int ns = min(cnt - seg, LY::SEG);
+    if (seg) __syncthreads();
+    const Staged st = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, list, tid, lane, NT);
+    const int n = st.chunks;
+    if (n == 0) continue;
+    __builtin_amdgcn_s_waitcnt(0);  // Q and list loads are done: only DMA is counted below
+    WalkCursor<LY::TAB_OFF, LY::T, true> cur(list, ns, st.stream);
+    auto next4 = [](int v) { return v + 4 >= LY::VRING ? v + 4 - LY::VRING : v + 4; };
+    int c_issue = sidx, v_issue = sidx;  // the next chunk to issue, its V slot
+    auto issue = [&]() {
+      if (c_issue < n) {
+        cur.advance(c_issue == sidx ? sidx + 1 : 4);
+        if (lane == 0) kval[c_issue & 15] = cur.keys();
+        int t[2];
+        uint32_t r[2];
+        cur.template look_up<2>(lds, lane_row, kx, t, r);
+        r[0] += t[0];
+        r[1] += t[1];
+        const uint32_t kd = lds_u32 + (c_issue & (LY::KRING - 1)) * LY::TILE;
+        const uint32_t vd = lds_u32 + LY::V_OFF + v_issue * LY::TILE;
+#pragma unroll
+        for (int k = 0; k < KV::LOADS; ++k) tile_dma(kbase, r[k & 1], kd, k);
+#pragma unroll
+        for (int k = 0; k < KV::LOADS; ++k) tile_dma(vbase, r[k & 1] + dvx, vd, k);
+      }
+      c_issue += 4;
+      v_issue = next4(v_issue);
+    };
+    int vs = sidx;  // V slot of the next chunk to compute
+    auto compute = [&](int c) {
+      if (rows_live && c < n)
+        lone_chunk<D>(x, kval[c & 15], scale_log2, lds,
+                      fr.k + (c & (LY::KRING - 1)) * LY::TILE, fr.v + LY::V_OFF + vs * LY::TILE);
+      vs = next4(vs);
+    };
+    issue();  // window 0
+    issue();  // window 1
+    if (sidx + 4 < n)
+      wait_loads<2 * KV::LOADS>();
+    else
+      wait_loads<0>();
+    __syncthreads();  // B_0: window 0 landed
+    const int nb = (n + 1) / 4;  // barriers B_1 .. B_nb of the walk
+#pragma unroll 1
+    for (int v = 1; v <= nb; ++v) {
+      compute(4 * (v - 1) + sidx);
+      wait_loads<0>();
+      __syncthreads();  // B_v: window v landed
+      issue();          // window v + 1
+    }
+    compute(4 * nb + sidx);
+  }
+
+  // tile 4: the Y waves' partial states merge in LDS
+  float* mg = reinterpret_cast<float*>(smem_raw);
+  __syncthreads();
+  if (sidx > 0 && rows_live) {
+    float* dst = mg + (sidx - 1) * (LY::MERGE_FLOATS * 64);
+#pragma unroll
+    for (int t = 0; t < KV::DT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dst[(t * 16 + r) * 64 + lane] = x.o[t][r];
+    dst[(KV::DT * 16) * 64 + lane] = x.m;
+    dst[(KV::DT * 16 + 1) * 64 + lane] = x.l;
+  }
+  __syncthreads();
+  if (sidx > 0) return;
+  if (rows_live) {
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+      const float* src = mg + k * (LY::MERGE_FLOATS * 64);
+      const float mB = src[(KV::DT * 16) * 64 + lane];
+      const float lB = src[(KV::DT * 16 + 1) * 64 + lane];
+      const float mm = fmaxf(x.m, mB);
+      const bool none = mm == -INFINITY;
+      const float aA = none ? 0.0f : __builtin_amdgcn_exp2f(x.m - mm);
+      const float aB = none ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
+#pragma unroll
+      for (int t = 0; t < KV::DT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          x.o[t][r] = x.o[t][r] * aA + src[(t * 16 + r) * 64 + lane] * aB;
+      x.l = x.l * aA + lB * aB;
+      x.m = mm;
+    }
+  }
+  store_tile<D, RASTER>(g, e_i, x, q0, head_row, first_row, ob, lse);
+}
+
+// Kernels. MULTI (raster only): one launch over heads with different blockings; the work
+// item picks its head, and with it the geometry and block lists, from `tab`. Blocks of 5
+// row tiles run the same walk under three names, which traces and the bench's label tell
+// apart: attn_sw_kernel (d = 128, lists of at most kSwBlocks blocks), attn_pp_kernel (d =
+// 64, or lists of at most kPpBlocks), attn_kernel (longer ones).
+#define SPADE_ATTN_ARGS                                                                       \
+  DevGeom g_arg, const uint4 *__restrict__ qb, const char *__restrict__ kb,                   \
+      const char *__restrict__ vb, const int *__restrict__ counts,                            \
+      const int *__restrict__ indices, float scale_log2, __bf16 *__restrict__ ob,             \
+      float *__restrict__ lse, const int *__restrict__ order,                                 \
+      typename std::conditional<MULTI, MultiTable, NoTable>::type tab
+constexpr int kSwBlocks = 3824, kPpBlocks = 7928;
+constexpr int kLoaderItems = 8192;
+
+template <int D, int W, bool RASTER, bool MULTI, bool STREAM>
+__global__ void __launch_bounds__(W == 5 ? 512 : 64 * W)
+    __attribute__((amdgpu_waves_per_eu(D == 64 && W != 5 ? 3 : 2))) attn_kernel(SPADE_ATTN_ARGS) {
+  extern __shared__ __align__(16) char smem_raw[];
+  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
+  if (it.i < 0) return;
+  if constexpr (W == 5)
+    five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
+  else
+    row_tile_walk<D, W, RASTER, STREAM>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
+}
+
+template <int D, int W, bool RASTER, bool MULTI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+    attn_sw_kernel(SPADE_ATTN_ARGS) {
+  extern __shared__ __align__(16) char smem_raw[];
+  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
+  if (it.i >= 0) five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
+}
+
+template <int D, int W, bool RASTER, bool MULTI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+    attn_pp_kernel(SPADE_ATTN_ARGS) {
+  extern __shared__ __align__(16) char smem_raw[];
+  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
+  if (it.i >= 0) five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
+}
+#undef SPADE_ATTN_ARGS
+
+// ---- the loader kernel ----
+
+template <int D>
+struct Tile {
+  static constexpr int NCH = D / 8;                 // 16-byte pieces per row
+  static constexpr int ROW_BYTES = D * 2;
+  static constexpr int TILE_BYTES = kChunk * ROW_BYTES;
+  static constexpr int RPI = 64 / NCH;              // rows per wave-wide 1 KB load
+  static constexpr int LOADS = kChunk / RPI;        // wave loads per tile
+  static constexpr int BUF_BYTES = 2 * TILE_BYTES;  // K tile then V tile
+};
+
+// swizzles: LDS piece c of tile row r holds global piece c ^ f(r)
+template <int D>
+__device__ __forceinline__ int swz_k(int r) { return r & (Tile<D>::NCH - 1); }
+// V: in a transposing read, lanes 0-15 take pieces 4t + {0,1} and lanes 16-31 pieces
+// 4t + {2,3} of rows 0-3; an XOR stride of 4 pieces (d = 128) keeps the two groups'
+// pieces disjoint, so 32 lanes hit 64 distinct banks (no LDS bank conflicts)
+template <int D>
+__device__ __forceinline__ int swz_v(int r) { return D >= 128 ? 4 * (r & 3) : 2 * (r & 3); }
+
+// Position in the kept-block walk: list entry jj, its block j and real-key count nj,
+// the chunk's first key slot c0, and block j's extent (raster addressing).
+struct Cursor {
+  int jj, j, nj, c0;
+  BlockExt e;
+};
+
+// Raster addressing of slot s of the cursor's block, relative to `base`: full
+// blocks (every block away from the grid's far edges) share one slot -> token
+// offset table `rel` (LDS, built once per workgroup), so a load costs one LDS
+// read instead of the division-based map; ragged blocks take the map.
+struct RasterRows {
+  bool full;
+  int64_t base;  // head_row + block origin (full), head_row (ragged)
+};
+
+__device__ __forceinline__ RasterRows raster_rows(const DevGeom& g, const Cursor& c,
+                                                  int64_t head_row) {
+  const bool full = c.e.n == g.BS;
+  return {full, head_row + (full ? block_origin(g, c.e) : 0)};
+}
+
+__device__ __forceinline__ Cursor next_chunk(const DevGeom& g, const lds_int* list, int cnt,
+                                             Cursor c) {
+  c.c0 += kChunk;
+  while (c.c0 >= c.nj) {
+    ++c.jj;
+    if (c.jj >= cnt) {
+      c.nj = 0;
+      c.c0 = 0;
+      return c;
+    }
+    const int j = __builtin_amdgcn_readfirstlane(list[c.jj]);  // uniform: keep in SGPRs
+    if (j >= 0 && j < g.NB) {
+      c.j = j;
+      c.e = block_ext(g, j);
+      c.nj = c.e.n;
+      c.c0 = 0;
+    }
+  }
+  return c;
+}
+
+// The 2*LOADS wave-wide DMA loads of one chunk: K and V rows at base_row + the lane's
+// row offsets (bytes), into the chunk's LDS buffer.
+template <int D>
+__device__ __forceinline__ void loader_issue(const char* kb, const char* vb, int64_t base_row,
+                                             const uint32_t (&row_off)[Tile<D>::LOADS],
+                                             uint32_t lds_buf, int lane) {
+  using TL = Tile<D>;
+  const char* kbase = kb + base_row * TL::ROW_BYTES;
+  const char* vbase = vb + base_row * TL::ROW_BYTES;
+#pragma unroll
+  for (int q = 0; q < 2 * TL::LOADS; ++q) {
+    const bool is_v = q >= TL::LOADS;
+    const int qq = is_v ? q - TL::LOADS : q;
+    const int r = qq * TL::RPI + lane / TL::NCH;  // tile row (key slot in chunk)
+    const int gp = (lane % TL::NCH) ^ (is_v ? swz_v<D>(r) : swz_k<D>(r));
+    const uint32_t off = row_off[qq] + uint32_t(gp * 16);
+    const uint32_t dst = lds_buf + (is_v ? TL::TILE_BYTES : 0) + qq * 1024;  // M0
+    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(is_v ? vbase : kbase),
+                 "{m0}"(dst)
+                 : "memory");
+  }
+}
+
+template <int D, bool RASTER>
+__device__ __forceinline__ void loader_chunk(const DevGeom& g, const char* kb, const char* vb,
+                                             int64_t head_row, const Cursor& c, const lds_int* rel,
+                                             uint32_t lds_buf, int lane) {
+  using TL = Tile<D>;
+  const int last = c.nj - 1 - c.c0;  // last real key slot of the chunk
+  uint32_t row_off[TL::LOADS];       // byte offset of this lane's row in load qq
+  int64_t base_row;
+  auto fill = [&](auto row_of) {
+#pragma unroll
+    for (int qq = 0; qq < TL::LOADS; ++qq)
+      row_off[qq] = uint32_t(row_of(min(qq * TL::RPI + lane / TL::NCH, last)) * TL::ROW_BYTES);
+  };
+  if (!RASTER) {
+    base_row = head_row + int64_t(c.j) * g.BS + c.c0;
+    fill([](int sr) { return sr; });
+  } else {
+    const RasterRows rr = raster_rows(g, c, head_row);
+    base_row = rr.base;
+    if (rr.full)
+      fill([&](int sr) { return rel[c.c0 + sr]; });
+    else
+      fill([&](int sr) { return int(ext_token(g, c.e, c.c0 + sr)); });
+  }
+  loader_issue<D>(kb, vb, base_row, row_off, lds_buf, lane);
+}
+
+// Single-buffered phases with a loader wave: W compute waves (32 query slots each) and one
+// more that issues all loads of the next chunk while this one is computed (two LDS
+// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the two shapes
+// where it beats the pipelined walk (see the dispatch).
+template <int D, int W, bool RASTER, bool MULTI>
+__global__ void __launch_bounds__(64 * (W + 1))
+    __attribute__((amdgpu_waves_per_eu(3)))
+    attn_loader_kernel(DevGeom g_arg, const uint4* __restrict__ qb, const char* __restrict__ kb,
                 const char* __restrict__ vb, const int* __restrict__ counts,
                 const int* __restrict__ indices, float scale_log2, __bf16* __restrict__ ob,
                 float* __restrict__ lse, const int* __restrict__ order,
@@ -390,7 +728,7 @@ __global__ void __launch_bounds__(64 * (W + LD))
   const int n_i = e_i.n;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keep in an SGPR
-  const bool loader = LD && wave == W;  // loader wave: q0 = 32 W >= BS, so no query rows
+  const bool loader = wave == W;  // loader wave: q0 = 32 W >= BS, so no query rows
   const int q0 = wave * 32;
   const int half = lane >> 5;  // k-slot group of the MFMA operands
   const int r32 = lane & 31;
@@ -414,9 +752,9 @@ __global__ void __launch_bounds__(64 * (W + LD))
   }
 
   const int cnt = min(max(*cnt_src, 0), g.NB);
-  for (int e = threadIdx.x; e < cnt; e += 64 * (W + LD)) list[e] = list_src[e];
+  for (int e = threadIdx.x; e < cnt; e += 64 * (W + 1)) list[e] = list_src[e];
   if (RASTER) {
-    for (int sl = threadIdx.x; sl < g.BS; sl += 64 * (W + LD)) {
+    for (int sl = threadIdx.x; sl < g.BS; sl += 64 * (W + 1)) {
       const int q = sl / g.bw;
       rel[sl] = ((q / g.bh) * g.Hs + q % g.bh) * g.Ws + sl % g.bw;
     }
@@ -443,47 +781,19 @@ __global__ void __launch_bounds__(64 * (W + LD))
   const bf16x2 ones = {__bf16(1.0f), __bf16(1.0f)};
 
   const uint32_t lds_u32 = uint32_t(reinterpret_cast<uintptr_t>(lds));
-  int rows[WaveLoads<D, W>::NQ];  // without a loader: this wave's rows of the next chunk
-  // issue the loads of chunk c into buffer b (all of them from the loader wave,
-  // or each wave its share at the rows prefetched into `rows`)
-  auto issue = [&](const Cursor& c, int b) {
-    if (LD) {
-      if (loader)
-        loader_chunk<D, RASTER>(g, kb, vb, head_row, c, rel, lds_u32 + b * TL::BUF_BYTES, lane);
-    } else {
-      load_chunk<D, W, RASTER>(g, kb, vb, head_row, c, rows, lds + b * TL::BUF_BYTES, wave, lane);
-    }
-  };
-  auto prefetch = [&](const Cursor& c) {
-    if (!LD) wave_rows<D, W, RASTER>(g, c, rel, wave, lane, rows);
+  auto issue = [&](const Cursor& c, int b) {  // the loads of chunk c into buffer b
+    if (loader)
+      loader_chunk<D, RASTER>(g, kb, vb, head_row, c, rel, lds_u32 + b * TL::BUF_BYTES, lane);
   };
   Cursor cur = {-1, 0, 0, -kChunk, e_i};
   cur = next_chunk(g, list, cnt, cur);
   int buf = 0;
-  if (cur.jj < cnt) {
-    prefetch(cur);
-    issue(cur, 0);
-  }
-  Cursor ahead = cur;  // without a loader: the chunk after the next, rows prefetched
-  if (!LD) {
-    ahead = next_chunk(g, list, cnt, cur);
-    if (ahead.jj < cnt) prefetch(ahead);
-  }
+  if (cur.jj < cnt) issue(cur, 0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   while (cur.jj < cnt) {
-    Cursor nxt;
-    if (LD) {
-      nxt = next_chunk(g, list, cnt, cur);
-      if (nxt.jj < cnt) issue(nxt, buf ^ 1);
-    } else {
-      nxt = ahead;
-      if (nxt.jj < cnt) {
-        issue(nxt, buf ^ 1);
-        ahead = next_chunk(g, list, cnt, nxt);
-        if (ahead.jj < cnt) prefetch(ahead);
-      }
-    }
+    const Cursor nxt = next_chunk(g, list, cnt, cur);
+    if (nxt.jj < cnt) issue(nxt, buf ^ 1);
     if (rows_live) {
       lds_char* Kt = lds + buf * TL::BUF_BYTES;
       lds_char* Vt = Kt + TL::TILE_BYTES;
@@ -605,940 +915,46 @@ __global__ void __launch_bounds__(64 * (W + LD))
   }
 }
 
-// Paired kernel (blocks of 5 row tiles, i.e. 129..160 slots). The waves of a
-// workgroup otherwise move through each chunk in step (LDS reads, S MFMAs,
-// softmax VALU, P.V MFMAs, barrier), so a SIMD's matrix and vector units take
-// turns instead of overlapping. Here each 32-row query tile has two compute
-// waves, placed on the same SIMD (waves w and w + 4 of a workgroup share one):
-// member A takes the even chunks of the kept walk, member B the odd ones, each
-// with its own online-softmax state, and the pair merges by log-sum-exp at the
-// end. A step has two halves separated by workgroup barriers:
-//   half 0: A runs P.V(2s-2) and S(2s) (MFMA), B the softmax of 2s-1 (VALU) and
-//           reads the V^T fragments of 2s-1 into registers;
-//   half 1: B runs P.V(2s-1) and S(2s+1), A the softmax of 2s and its V^T reads;
-// so on every SIMD one member's matrix work meets the other's vector work. Two
-// loader waves (even / odd chunks) keep an 8-chunk LDS ring three chunks ahead;
-// a slot is refilled in the half after its V^T was read.
-// One workgroup (12 waves) fills a CU. With 4 row tiles the pairs would leave a
-// CU at 8 compute waves instead of 12, which is slower, so smaller blocks keep
-// the single-member kernel.
-constexpr int kRing = 8;
-constexpr int kPairTiles = 5;         // row tiles of the blocks the paired kernel takes
-constexpr int kPairLds = 160 * 1024;  // LDS of one CU, all of it for one workgroup
-
-template <int D>
-struct PPLayout {
-  static constexpr int RING_BYTES = kRing * Tile<D>::BUF_BYTES;
-  static constexpr int REL_OFF = RING_BYTES;
-  static constexpr int KVAL_OFF = RING_BYTES + kMaxBS * 4;  // real keys per ring slot
-  static constexpr int LIST_OFF = KVAL_OFF + kRing * 4;
-  static constexpr int LPC = 2 * Tile<D>::LOADS;  // loads per chunk (one loader wave)
-  static constexpr int MERGE_FLOATS = D / 32 * 16 + 2;  // per lane: O, m, l
-};
-
-// (tile, phase) of compute wave w of 2T: full octets pair w with w + 4.
-__device__ __forceinline__ void pp_role(int w, int T, int* tile, int* ph) {
-  const int full = (2 * T) / 8 * 8;
-  if (w < full) {
-    *tile = (w / 8) * 4 + (w & 3);
-    *ph = (w >> 2) & 1;
-  } else {
-    const int h = (2 * T - full) / 2, r = w - full;
-    *tile = full / 2 + r % h;
-    *ph = r >= h;
+// Whether walking a geometry's keys as one stream saves at least 3% of its chunks: the
+// look-up of chunks that span two blocks costs 2-4% (128-slot blocks whose edge blocks
+// are multiples of 32 keys: 2.67 against 2.74 ms; 120-slot blocks: 26.8 ms with the
+// stream against 28.6 without it).
+// Blocks of fewer than 32 keys keep a list from being a stream, so they count as kept.
+bool saves_chunks(const DevGeom& g) {
+  int64_t chunks = 0, keys = 0;
+  for (int k = 0; k < 8; ++k) {  // full or ragged along each axis
+    const int et = (k & 1) ? g.T % g.bt : g.bt, eh = (k & 2) ? g.Hs % g.bh : g.bh;
+    const int ew = (k & 4) ? g.Ws % g.bw : g.bw;
+    const int64_t n = int64_t(et) * eh * ew;
+    const int64_t count = int64_t((k & 1) ? 1 : g.T / g.bt) * ((k & 2) ? 1 : g.Hs / g.bh) *
+                          ((k & 4) ? 1 : g.Ws / g.bw);
+    const int64_t c = (n + kChunk - 1) / kChunk;
+    chunks += count * c;
+    keys += count * (n < kChunk ? c * kChunk : n);
   }
+  return 100 * (chunks * kChunk - keys) >= 3 * chunks * kChunk;
 }
 
-// wait until at most n chunks' loads (n = 0, 1, 2) of this wave are in flight
-template <int LPC>
-__device__ __forceinline__ void wait_chunks(int n) {
-  constexpr auto imm = [](int c) { return (c & 15) | (((c >> 4) & 3) << 14) | 0x70 | 0xF00; };
-  if (n <= 0)
-    __builtin_amdgcn_s_waitcnt(imm(0));
-  else if (n == 1)
-    __builtin_amdgcn_s_waitcnt(imm(LPC));
-  else
-    __builtin_amdgcn_s_waitcnt(imm(2 * LPC));
-}
-
-template <int D, int T, bool RASTER, bool MULTI>
-__global__ void __launch_bounds__(64 * (2 * T + 2)) __attribute__((amdgpu_waves_per_eu(3)))
-    attn_pp_kernel(DevGeom g_arg, const uint4* __restrict__ qb, const char* __restrict__ kb,
-                   const char* __restrict__ vb, const int* __restrict__ counts,
-                   const int* __restrict__ indices, float scale_log2, __bf16* __restrict__ ob,
-                   float* __restrict__ lse, const int* __restrict__ order,
-                   typename std::conditional<MULTI, MultiTable, NoTable>::type tab) {
-  using TL = Tile<D>;
-  using LY = PPLayout<D>;
-  constexpr int NT = 64 * (2 * T + 2);
-  extern __shared__ __align__(16) char smem_raw[];
-  lds_char* const lds = (lds_char*)smem_raw;
-  lds_int* const rel = (lds_int*)(smem_raw + LY::REL_OFF);
-  lds_int* const list = (lds_int*)(smem_raw + LY::LIST_OFF);
-  lds_int* const kval = (lds_int*)(smem_raw + LY::KVAL_OFF);
-
-  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
-  if (it.i < 0) return;
-  const DevGeom g = it.g;
-  const int64_t bh = it.bh;
-  const int i = it.i;
-  const BlockExt e_i = block_ext(g, i);
-  const int n_i = e_i.n;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool loader = wave >= 2 * T;
-  const int lp = wave - 2 * T;  // loader parity: 0 even chunks, 1 odd
-  int tile = T, ph = 0;          // loaders own no rows (32 T >= BS)
-  if (!loader) pp_role(wave, T, &tile, &ph);
-  tile = __builtin_amdgcn_readfirstlane(tile);
-  ph = __builtin_amdgcn_readfirstlane(ph);
-  const int q0 = tile * 32;
-  const int half = lane >> 5, r32 = lane & 31;
-  const int64_t head_row = RASTER ? bh * g.N : bh * g.NB * int64_t(g.BS);
-  auto q_row = [&](int qs) -> int64_t {
-    return RASTER ? head_row + ext_token(g, e_i, qs) : head_row + int64_t(i) * g.BS + qs;
-  };
-
-  bf16x8 qf[D / 16];
-  {
-    const int qs = q0 + r32;
-    const uint4* src = qb + q_row(min(qs, n_i - 1)) * TL::NCH + half;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (qs < n_i) v = src[2 * kk];
-      qf[kk] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  const int cnt = min(max(*it.cnt_src, 0), g.NB);
-  for (int e = tid; e < cnt; e += NT) list[e] = it.list_src[e];
-  if (RASTER) {
-    for (int sl = tid; sl < g.BS; sl += NT) {
-      const int q = sl / g.bw;
-      rel[sl] = ((q / g.bh) * g.Hs + q % g.bh) * g.Ws + sl % g.bw;
-    }
-  }
-  __syncthreads();
-
-  // chunks of the kept walk (every wave computes the same count)
-  int nch = 0;
-  for (int e = lane; e < cnt; e += 64) {
-    const int j = list[e];
-    if (j >= 0 && j < g.NB) nch += (block_ext(g, j).n + kChunk - 1) / kChunk;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) nch += __shfl_xor(nch, off);
-  nch = __builtin_amdgcn_readfirstlane(nch);
-
-  const int v_row0 = 4 * ((lane >> 4) >> 1) + ((lane & 15) >> 2);
-  const int v_piece0 = 2 * ((lane >> 4) & 1) + (((lane & 15) & 3) >> 1);
-  const int v_sub = (lane & 1) * 8;
-  const int k_off = r32 * TL::ROW_BYTES;
-  const int k_sw = swz_k<D>(r32);
-
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
-  const bool rows_live = !loader && q0 < n_i;
-  const bf16x2 ones = {__bf16(1.0f), __bf16(1.0f)};
-  const uint32_t lds_u32 = uint32_t(reinterpret_cast<uintptr_t>(lds));
-  auto kbuf = [&](int k) { return lds + (k & (kRing - 1)) * TL::BUF_BYTES; };
-
-  auto compute_s = [&](int k) {
-    lds_char* Kt = kbuf(k);
-    f32x16 sv;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sv[r] = 0.0f;
-    bf16x8 kf[D / 16];
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-      kf[kk] = *(lds_bf16x8*)(Kt + k_off + (((2 * kk + half) ^ k_sw) << 4));
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-      sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sv, 0, 0, 0);
-#pragma unroll
-    for (int gi = 0; gi < D / 32; ++gi) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    }
-    return sv;
-  };
-  bf16x8 p[2];
-  auto softmax = [&](f32x16 sv, int c0, int nj) {
-    if (c0 + kChunk > nj) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int kr = (r >> 2) * 8 + 4 * half + (r & 3);
-        if (c0 + kr >= nj) sv[r] = -INFINITY;
-      }
-    }
-    float mx = sv[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sv[r]);
-    {
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
-                                                       false, false);
-      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2;
-    }
-    if (__any(mx > m + kRescaleLog2)) {
-      const float mnew = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-      l *= alpha;
-#pragma unroll
-      for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
-      m = mnew;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], scale_log2, -m));
-      p[r >> 3][r & 7] = __bf16(e);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bf16x2 pr = {p[u][2 * e], p[u][2 * e + 1]};
-        l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
-      }
-  };
-  // V^T fragments of a chunk are read at the end of the vector phase that made its P
-  // (S is dead by then), so the matrix phase starts on MFMAs instead of an LDS round
-  // trip; they stay in registers across the barrier.
-  bf16x8 vf[D / 32][2];
-  auto read_v = [&](int k) {
-    __builtin_amdgcn_sched_barrier(0);
-    lds_char* Vt = kbuf(k) + TL::TILE_BYTES;
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        bf16x4 h2[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = 16 * u + 8 * h + v_row0;
-          const int piece = (4 * t + v_piece0) ^ swz_v<D>(row);
-          h2[h] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-              (lds_bf16x4*)(Vt + row * TL::ROW_BYTES + piece * 16 + v_sub));
-        }
-        vf[t][u] = __builtin_shufflevector(h2[0], h2[1], 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-  };
-  auto pv = [&]() {
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][u], p[u], o[t], 0, 0, 0);
-  };
-
-  // Loaders keep a cursor on chunk 2s + par of step s, three chunks ahead (the next
-  // one they issue), and record each chunk's real keys beside its ring slot, so the
-  // compute waves mask without walking the kept list themselves.
-  const int par = loader ? lp : ph;
-  auto next2 = [&](Cursor c) { return next_chunk(g, list, cnt, next_chunk(g, list, cnt, c)); };
-  Cursor cur{};
-  if (loader) {
-    cur = next_chunk(g, list, cnt, {-1, 0, 0, -kChunk, e_i});
-    if (par == 1) cur = next_chunk(g, list, cnt, cur);
-  }
-  auto record = [&](int k) {
-    if (lane == 0) kval[k & (kRing - 1)] = min(cur.nj - cur.c0, kChunk);
-  };
-  auto issue = [&](int k) {
-    record(k);
-    loader_chunk<D, RASTER>(g, kb, vb, head_row, cur, rel,
-                            lds_u32 + (k & (kRing - 1)) * TL::BUF_BYTES, lane);
-  };
-  if (loader) {
-#pragma unroll 1
-    for (int r = 0; r < 3; ++r) {
-      if (par + 2 * r < nch) issue(par + 2 * r);
-      cur = next2(cur);
-    }
-    if (par == 0) wait_chunks<LY::LPC>((2 < nch) + (4 < nch));
-  }
-  const f32x16 zero16 = {};
-  const bf16x8 zero8 = {};
-  const int sc0 = 0;  // the held S covers keys 0 .. snj - 1 of its chunk
-  int snj = 0;
-  f32x16 sv = zero16;
-  const int steps = nch > 0 ? (nch + 1) / 2 + 1 : 0;
-  // Each role runs its own loop (so S and P are never live across each other's
-  // phases); all three execute the same two barriers per step. In the matrix
-  // phase P.V of the previous own chunk (its V^T already in registers) runs before
-  // S of this one.
-  __syncthreads();
-  if (loader) {
-    // Raster layout: the row offsets of a full block's chunk depend only on the
-    // chunk's position in the block (T positions), so they are read from the slot
-    // table once here; the loop then issues full-block chunks without LDS reads,
-    // which would queue behind the compute waves' K and V^T reads.
-    uint32_t pre[RASTER ? T : 1][TL::LOADS];
-    if (RASTER) {
-#pragma unroll
-      for (int ps = 0; ps < T; ++ps)
-#pragma unroll
-        for (int qq = 0; qq < TL::LOADS; ++qq) {
-          const int sr = min(qq * TL::RPI + lane / TL::NCH, max(g.BS - 1 - ps * kChunk, 0));
-          pre[ps][qq] = uint32_t(rel[min(ps * kChunk + sr, g.BS - 1)] * TL::ROW_BYTES);
-        }
-    }
-    auto issue_loop = [&](int k) {
-      record(k);
-      const uint32_t buf = lds_u32 + (k & (kRing - 1)) * TL::BUF_BYTES;
-      if (RASTER && cur.e.n == g.BS) {
-        uint32_t ro[TL::LOADS];
-        const int ps = cur.c0 / kChunk;
-#pragma unroll
-        for (int pp = 0; pp < T; ++pp)
-          if (pp == ps)
-#pragma unroll
-            for (int qq = 0; qq < TL::LOADS; ++qq) ro[qq] = pre[RASTER ? pp : 0][qq];
-        loader_issue<D>(kb, vb, head_row + block_origin(g, cur.e), ro, buf, lane);
-      } else {
-        loader_chunk<D, RASTER>(g, kb, vb, head_row, cur, rel, buf, lane);
-      }
-    };
-#pragma unroll 1
-    for (int st = 0; st < steps; ++st) {
-      const int k = 2 * st + par;
-      // half 0: loader 0 refills the slot of chunk 2s - 2 (its V^T was read in the
-      // previous half 1); loader 1 makes sure chunk 2s + 1 (read in half 1) has landed
-      if (par == 0 && k + 6 < nch) issue_loop(k + 6);
-      if (par == 1 && k < nch) wait_chunks<LY::LPC>((k + 2 < nch) + (k + 4 < nch));
-      __syncthreads();
-      // half 1: loader 1 refills the slot of chunk 2s - 1 (V^T read in half 0); loader 0
-      // makes sure chunk 2s + 2 (read in the next half 0) has landed
-      if (par == 1 && k + 6 < nch) issue_loop(k + 6);
-      if (par == 0 && k + 2 < nch) wait_chunks<LY::LPC>((k + 4 < nch) + (k + 6 < nch));
-      __syncthreads();
-      cur = next2(cur);
-    }
-  } else if (par == 0) {
-#pragma unroll 1
-    for (int st = 0; st < steps; ++st) {
-      const int k = 2 * st;
-      // half 0: matrix phase
-      if (rows_live && k >= 2 && k - 2 < nch) pv();
-      if (rows_live && k < nch) {
-        sv = compute_s(k);
-        snj = kval[k & (kRing - 1)];
-      } else {
-        sv = zero16;
-      }
-      __syncthreads();
-      // half 1: vector phase
-      if (rows_live && k < nch) {
-        softmax(sv, sc0, snj);
-        read_v(k);
-      } else {
-        p[0] = zero8;
-        p[1] = zero8;
-#pragma unroll
-        for (int t = 0; t < D / 32; ++t) vf[t][0] = vf[t][1] = zero8;
-      }
-      __syncthreads();
-    }
-  } else {
-#pragma unroll 1
-    for (int st = 0; st < steps; ++st) {
-      const int k = 2 * st + 1;
-      // half 0: vector phase (the S computed in the previous step's half 1)
-      if (rows_live && k >= 2 && k - 2 < nch) {
-        softmax(sv, sc0, snj);
-        read_v(k - 2);
-      } else {
-        p[0] = zero8;
-        p[1] = zero8;
-#pragma unroll
-        for (int t = 0; t < D / 32; ++t) vf[t][0] = vf[t][1] = zero8;
-      }
-      __syncthreads();
-      // half 1: matrix phase
-      if (rows_live && k >= 2 && k - 2 < nch) pv();
-      if (rows_live && k < nch) {
-        sv = compute_s(k);
-        snj = kval[k & (kRing - 1)];
-      } else {
-        sv = zero16;
-      }
-      __syncthreads();
-    }
-  }
-
-  // merge: member B hands (O, m, l) to member A of its tile through LDS
-  float* mg = reinterpret_cast<float*>(smem_raw) + tile * (LY::MERGE_FLOATS * 64);
-  if (rows_live && ph == 1) {
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mg[(t * 16 + r) * 64 + lane] = o[t][r];
-    mg[(D / 32 * 16) * 64 + lane] = m;
-    mg[(D / 32 * 16 + 1) * 64 + lane] = l;
-  }
-  __syncthreads();
-  if (loader || ph == 1) return;
-  if (rows_live) {
-    const float mB = mg[(D / 32 * 16) * 64 + lane];
-    const float lB = mg[(D / 32 * 16 + 1) * 64 + lane];
-    const float mm = fmaxf(m, mB);
-    const bool none = mm == -INFINITY;
-    const float aA = none ? 0.0f : __builtin_amdgcn_exp2f(m - mm);
-    const float aB = none ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[t][r] = o[t][r] * aA + mg[(t * 16 + r) * 64 + lane] * aB;
-    l = l * aA + lB * aB;
-    m = mm;
-  }
-  {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l),
-                                                     false, false);
-    l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  }
-  const int qs = q0 + r32;
-  if (RASTER ? qs < n_i : qs < g.BS) {
-    const bool real = qs < n_i;
-    const float inv = (real && l > 0.0f) ? 1.0f / l : 0.0f;
-    const int64_t orow = real ? q_row(qs) : head_row + int64_t(i) * g.BS + qs;
-    __bf16* dst = ob + orow * D + 4 * half;
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __bf16(o[t][4 * rq + e] * inv);
-        *reinterpret_cast<bf16x4*>(dst + 32 * t + 8 * rq) = v;
-      }
-    if (lse && real && half == 0)
-      lse[orow] = l > 0.0f ? (m + log2f(l)) * 0.69314718055994530942f : -INFINITY;
-  }
-}
-
-template <int D, int T, bool RASTER, bool MULTI>
-hipError_t launch_pp(const DevGeom& g, const void* qb, const void* kb, const void* vb,
-                     const int* counts, const int* indices, float scale_log2, void* ob,
-                     float* lse, hipStream_t s, const MultiTable* tab, const int* order,
-                     int nb_max) {
-  {  // the ring and the kept list exceed the 64 KB default
-    const hipError_t e = ensure_dynamic_lds(
-        reinterpret_cast<const void*>(&attn_pp_kernel<D, T, RASTER, MULTI>), kPairLds);
-    if (e != hipSuccess) return e;
-  }
-  const size_t lds = size_t(PPLayout<D>::LIST_OFF) + size_t(nb_max) * sizeof(int);
+// Launches `kernel` (one of the above, all with the same arguments) over the work items.
+template <bool MULTI, class Kernel>
+hipError_t launch_items(Kernel kernel, int threads, size_t lds, int max_lds, const DevGeom& g,
+                        const void* qb, const void* kb, const void* vb, const int* counts,
+                        const int* indices, float scale_log2, void* ob, float* lse, hipStream_t s,
+                        const MultiTable* tab, const int* order) {
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), max_lds);
+  if (e != hipSuccess) return e;
   const uint4* q4 = static_cast<const uint4*>(qb);
   const char* k1 = static_cast<const char*>(kb);
   const char* v1 = static_cast<const char*>(vb);
   __bf16* o2 = static_cast<__bf16*>(ob);
   if constexpr (MULTI) {
     const int64_t items = int64_t(g.B) * tab->items_per_batch;
-    attn_pp_kernel<D, T, RASTER, MULTI><<<dim3(unsigned(items)), 64 * (2 * T + 2), lds, s>>>(
-        g, q4, k1, v1, nullptr, nullptr, scale_log2, o2, lse, order, *tab);
+    kernel<<<dim3(unsigned(items)), threads, lds, s>>>(g, q4, k1, v1, nullptr, nullptr, scale_log2,
+                                                       o2, lse, order, *tab);
   } else {
     const int64_t items = int64_t(g.B) * g.H * ((g.NB + 7) / 8) * 8;  // see the XCD mapping
-    attn_pp_kernel<D, T, RASTER, MULTI><<<dim3(unsigned(items)), 64 * (2 * T + 2), lds, s>>>(
-        g, q4, k1, v1, counts, indices, scale_log2, o2, lse, order, NoTable{});
-  }
-  return hipGetLastError();
-}
-
-// Software-pipelined kernel (blocks of 5 row tiles, i.e. 129..160 slots, d = 128).
-// Eight waves, two per SIMD (waves w and w + 4 share one):
-// - wave X_s (s = 0..3) owns query tile s for the whole kept walk. Its chunk loop
-//   is pipelined by one chunk: while the softmax of chunk c runs on the vector
-//   unit, the matrix unit takes P.V of chunk c-1 and S of chunk c+1 (independent
-//   of that softmax), and the K fragments of c+1 and the V^T fragments of c are
-//   read from LDS in between. One wave issues its own MFMAs and vector work
-//   interleaved; no barrier pairs it with another wave.
-// - wave Y_s issues the DMA of every fourth chunk (s, s + 4, ...) and computes
-//   tile 4 on those same chunks with its own online-softmax state; the four
-//   partial states of tile 4 merge by log-sum-exp at the end in a fixed order. So
-//   every SIMD carries 1.25 tiles of work.
-// The waves meet at one barrier per window of four chunks. A 9-slot LDS ring
-// holds the window being computed, the chunk before it and the next window in
-// flight: chunk c lives in slot c % 9; Y_s issues window v + 1 right after the
-// barrier that opens window v and waits for it before the next barrier. X's
-// iteration c reads K of c + 1 and V^T of c, so the barrier that makes window v
-// visible sits before X's iteration 4v - 1.
-constexpr int kSwRing = 9;
-constexpr int kSwWaves = 8;
-constexpr int kSwTiles = 5;
-constexpr int kSwLds = 160 * 1024;
-
-template <int D>
-struct SwLayout {
-  static constexpr int RING_BYTES = kSwRing * Tile<D>::BUF_BYTES;
-  static constexpr int REL_OFF = RING_BYTES;
-  static constexpr int KVAL_OFF = REL_OFF + kMaxBS * 4;  // real keys per ring slot
-  static constexpr int LIST_OFF = KVAL_OFF + 64;
-  static constexpr int LPC = 2 * Tile<D>::LOADS;          // DMA loads per chunk
-  static constexpr int MERGE_FLOATS = D / 32 * 16 + 2;    // per lane: O, m, l
-};
-
-template <int D, int T, bool RASTER, bool MULTI>
-__global__ void __launch_bounds__(64 * kSwWaves) __attribute__((amdgpu_waves_per_eu(2)))
-    attn_sw_kernel(DevGeom g_arg, const uint4* __restrict__ qb, const char* __restrict__ kb,
-                   const char* __restrict__ vb, const int* __restrict__ counts,
-                   const int* __restrict__ indices, float scale_log2, __bf16* __restrict__ ob,
-                   float* __restrict__ lse, const int* __restrict__ order,
-                   typename std::conditional<MULTI, MultiTable, NoTable>::type tab) {
-  static_assert(T == kSwTiles, "blocks of 5 row tiles");
-  using TL = Tile<D>;
-  using LY = SwLayout<D>;
-  constexpr int NT = 64 * kSwWaves;
-  extern __shared__ __align__(16) char smem_raw[];
-  lds_char* const lds = (lds_char*)smem_raw;
-  lds_int* const rel = (lds_int*)(smem_raw + LY::REL_OFF);
-  lds_int* const list = (lds_int*)(smem_raw + LY::LIST_OFF);
-  lds_int* const kval = (lds_int*)(smem_raw + LY::KVAL_OFF);
-
-  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
-  if (it.i < 0) return;
-  const DevGeom g = it.g;
-  const int64_t bh = it.bh;
-  const int i = it.i;
-  const BlockExt e_i = block_ext(g, i);
-  const int n_i = e_i.n;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool is_y = wave >= 4;
-  const int sidx = wave & 3;          // X: tile; Y: chunk residue mod 4
-  const int tile = is_y ? 4 : sidx;   // Y waves share tile 4
-  const int q0 = tile * 32;
-  const bool rows_live = tile < T && q0 < n_i;
-  const int half = lane >> 5, r32 = lane & 31;
-  const int64_t head_row = RASTER ? bh * g.N : bh * g.NB * int64_t(g.BS);
-  auto q_row = [&](int qs) -> int64_t {
-    return RASTER ? head_row + ext_token(g, e_i, qs) : head_row + int64_t(i) * g.BS + qs;
-  };
-
-  bf16x8 qf[D / 16];
-  {
-    const int qs = q0 + r32;
-    const uint4* src = qb + q_row(min(qs, n_i - 1)) * TL::NCH + half;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (rows_live && qs < n_i) v = src[2 * kk];
-      qf[kk] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  const int cnt = min(max(*it.cnt_src, 0), g.NB);
-  for (int e = tid; e < cnt; e += NT) list[e] = it.list_src[e];
-  if (RASTER) {
-    for (int sl = tid; sl < g.BS; sl += NT) {
-      const int q = sl / g.bw;
-      rel[sl] = ((q / g.bh) * g.Hs + q % g.bh) * g.Ws + sl % g.bw;
-    }
-  }
-  __syncthreads();
-
-  // chunks of the kept walk (every wave computes the same count)
-  int nch = 0;
-  for (int e = lane; e < cnt; e += 64) {
-    const int j = list[e];
-    if (j >= 0 && j < g.NB) nch += (block_ext(g, j).n + kChunk - 1) / kChunk;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) nch += __shfl_xor(nch, off);
-  nch = __builtin_amdgcn_readfirstlane(nch);
-  const int nbar = nch / 4 + 1;  // barriers of the chunk walk, the same for every wave
-
-  const int v_row0 = 4 * ((lane >> 4) >> 1) + ((lane & 15) >> 2);
-  const int v_piece0 = 2 * ((lane >> 4) & 1) + (((lane & 15) & 3) >> 1);
-  const int v_sub = (lane & 1) * 8;
-  const int k_off = r32 * TL::ROW_BYTES;
-  const int k_sw = swz_k<D>(r32);
-
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
-  const bf16x2 ones = {__bf16(1.0f), __bf16(1.0f)};
-  const uint32_t lds_u32 = uint32_t(reinterpret_cast<uintptr_t>(lds));
-  auto slot = [](int c) { return c % kSwRing; };
-  // the slot's base as an opaque uniform value: the compiler then adds it once per
-  // distinct lane offset instead of folding the modulo into every read address
-  auto kbuf = [&](int c) {
-    return lds + __builtin_amdgcn_readfirstlane(slot(c) * TL::BUF_BYTES);
-  };
-
-  // per-lane LDS byte offsets of the fragment reads inside a ring slot, so each read
-  // costs one add of the slot base: K fragment kk (row r32, piece 2 kk + half), and
-  // the V^T fragments of output tile t (rows 16 u + 8 h + v_row0 share row & 3, so
-  // their swizzle, and the (u, h) part goes into the instruction's offset field)
-  int kofs[D / 16], vofs[D / 32];
-#pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) kofs[kk] = k_off + (((2 * kk + half) ^ k_sw) << 4);
-#pragma unroll
-  for (int t = 0; t < D / 32; ++t)
-    vofs[t] = TL::TILE_BYTES + v_row0 * TL::ROW_BYTES +
-              ((4 * t + v_piece0) ^ swz_v<D>(v_row0)) * 16 + v_sub;
-  auto read_k = [&](int c, bf16x8 (&kf)[D / 16]) {
-    lds_char* Kt = kbuf(c);
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *(lds_bf16x8*)(Kt + kofs[kk]);
-  };
-  auto read_v = [&](int c, bf16x8 (&vf)[D / 32][2]) {
-    lds_char* Vb = kbuf(c);
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t) {
-      lds_char* Vt = Vb + vofs[t];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        bf16x4 h2[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          h2[h] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-              (lds_bf16x4*)(Vt + (16 * u + 8 * h) * TL::ROW_BYTES));
-        vf[t][u] = __builtin_shufflevector(h2[0], h2[1], 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    }
-  };
-  // keys past the chunk's real ones get -inf (key of s[r]: (r/4)*8 + 4*half + r%4)
-  auto mask = [&](f32x16& sv, int kv) {
-    if (kv < kChunk) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int kr = (r >> 2) * 8 + 4 * half + (r & 3);
-        if (kr >= kv) sv[r] = -INFINITY;
-      }
-    }
-  };
-  // online softmax of one chunk: P (bf16) and the new running max; returns the
-  // factor that O must be scaled by (1 unless the max grew by more than 2^8)
-  auto softmax = [&](const f32x16& sv, bf16x8 (&p)[2], bool* rescale) {
-    float mx = sv[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sv[r]);
-    {
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
-                                                       false, false);
-      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2;
-    }
-    const bool rs = __any(mx > m + kRescaleLog2);
-    const float mnew = rs ? fmaxf(m, mx) : m;
-    const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-    m = mnew;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], scale_log2, -m));
-      p[r >> 3][r & 7] = __bf16(e);
-    }
-    float ls = l * alpha;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bf16x2 pr = {p[u][2 * e], p[u][2 * e + 1]};
-        ls = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, ls, false);
-      }
-    l = ls;
-    *rescale = rs;
-    return alpha;
-  };
-  auto scale_o = [&](float alpha) {
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
-  };
-  auto pv = [&](const bf16x8 (&vf)[D / 32][2], const bf16x8 (&p)[2]) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int t = 0; t < D / 32; ++t)
-        o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][u], p[u], o[t], 0, 0, 0);
-  };
-  auto s_of = [&](const bf16x8 (&kf)[D / 16]) {
-    f32x16 sv = {};
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk)
-      sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], sv, 0, 0, 0);
-    return sv;
-  };
-
-  if (!is_y) {
-    // ---- X: tile `tile`, every chunk, pipelined by one chunk ----
-    // One pipeline step for chunk c. In: S of c (svi), P and V^T of c - 1 (pi, vfi),
-    // and the rescale that the softmax of c - 1 asked for. Out: S of c + 1 (svo), P
-    // and V^T of c (po, vfo); the compiler folds most of the hand-over into the
-    // register allocation (a loop unrolled by two with the sets swapped spilled).
-    bool rs = false;
-    float alpha = 1.0f;
-    // kv: real keys of chunk c, read one step ahead and moved to a scalar register
-    // beside the K fragments' wait, so the mask test at the top of a step waits on no
-    // LDS read (a wait there would also drain the V^T reads just issued)
-    int kv = 0;
-    auto step = [&](int c, f32x16& svi, f32x16& svo, bf16x8 (&pi)[2], bf16x8 (&po)[2],
-                    bf16x8 (&vfi)[D / 32][2], bf16x8 (&vfo)[D / 32][2]) {
-      if ((c & 3) == 3) __syncthreads();  // window (c + 1) / 4 landed
-      const int kv_next = kval[slot(c + 1)];
-      if (rs) scale_o(alpha);  // O holds P.V up to c - 2; P of c - 1 used the new max
-      mask(svi, kv);
-      // part 1: the K fragments of c + 1 (past the walk's end the slot's stale
-      // contents: that S is discarded); P.V of c - 1 on the matrix unit; on the
-      // vector unit the row sum of P of c - 1, the row max of c and the first half of
-      // its exponentials
-      lds_char* Kt = kbuf(c + 1);
-      bf16x8 kf[D / 16];
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *(lds_bf16x8*)(Kt + kofs[kk]);
-      pv(vfi, pi);
-      {
-        float ls = l * alpha;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bf16x2 pr = {pi[u][2 * e], pi[u][2 * e + 1]};
-            ls = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, ls, false);
-          }
-        l = ls;
-      }
-      {
-        float mx = svi[0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, svi[r]);
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx),
-                                                         __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * scale_log2;
-        rs = __any(mx > m + kRescaleLog2);
-        const float mnew = rs ? fmaxf(m, mx) : m;
-        alpha = __builtin_amdgcn_exp2f(m - mnew);
-        m = mnew;
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-        po[0][r] = __bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(svi[r], scale_log2, -m)));
-      // part 2: S of c + 1 (two accumulators: two short MFMA chains), the V^T
-      // fragments of c and the second half of the exponentials
-      read_v(c, vfo);
-      f32x16 s0 = {}, s1 = {};
-#pragma unroll
-      for (int kk = 0; kk < D / 16; kk += 2) {
-        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk + 1], qf[kk + 1], s1, 0, 0, 0);
-      }
-      kv = __builtin_amdgcn_readfirstlane(kv_next);
-#pragma unroll
-      for (int r = 8; r < 16; ++r)
-        po[1][r - 8] = __bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(svi[r], scale_log2, -m)));
-#pragma unroll
-      for (int r = 0; r < 16; ++r) svo[r] = s0[r] + s1[r];
-    };
-    __syncthreads();  // window 0 landed
-    f32x16 svA = {}, svB = {};
-    bf16x8 pA[2] = {}, pB[2] = {};              // P of the previous chunk (zero before 0)
-    bf16x8 vfA[D / 32][2] = {}, vfB[D / 32][2] = {};  // V^T of the previous chunk
-    if (rows_live && nch > 0) {
-      bf16x8 kf[D / 16];
-      read_k(0, kf);
-      svA = s_of(kf);
-      kv = __builtin_amdgcn_readfirstlane(kval[slot(0)]);
-    }
-    // the last chunk's P.V (after the rescale its softmax asked for)
-    auto finish = [&](bf16x8 (&vfx)[D / 32][2], bf16x8 (&px)[2]) {
-      if (rs) scale_o(alpha);
-      pv(vfx, px);
-      float ls = l * alpha;
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const bf16x2 pr = {px[u][2 * e], px[u][2 * e + 1]};
-          ls = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, ls, false);
-        }
-      l = ls;
-    };
-    if (rows_live) {
-#pragma unroll 1
-      for (int c = 0; c < nch; ++c) {
-        step(c, svA, svB, pA, pB, vfA, vfB);
-        svA = svB;
-        pA[0] = pB[0];
-        pA[1] = pB[1];
-#pragma unroll
-        for (int t = 0; t < D / 32; ++t) {
-          vfA[t][0] = vfB[t][0];
-          vfA[t][1] = vfB[t][1];
-        }
-      }
-      if (nch > 0) finish(vfA, pA);
-    } else {  // no query rows here: only the barriers of the walk
-#pragma unroll 1
-      for (int c = 3; c < nch; c += 4) __syncthreads();
-    }
-  } else {
-    // ---- Y: DMA of chunks sidx, sidx + 4, ...; tile 4 on the same chunks ----
-    Cursor cur = next_chunk(g, list, nch > 0 ? cnt : 0, {-1, 0, 0, -kChunk, e_i});
-    auto advance4 = [&]() {
-#pragma unroll 1
-      for (int a = 0; a < 4; ++a) cur = next_chunk(g, list, cnt, cur);
-    };
-#pragma unroll 1
-    for (int a = 0; a < sidx; ++a) cur = next_chunk(g, list, cnt, cur);
-    int c_issue = sidx;  // next chunk this wave issues
-    auto issue = [&]() {
-      if (c_issue < nch) {
-        if (lane == 0) kval[slot(c_issue)] = min(cur.nj - cur.c0, kChunk);
-        loader_chunk<D, RASTER>(g, kb, vb, head_row, cur, rel,
-                                lds_u32 + slot(c_issue) * TL::BUF_BYTES, lane);
-        advance4();
-      }
-      c_issue += 4;
-    };
-    auto tile4 = [&](int c) {
-      if (rows_live && c < nch) {
-        bf16x8 kf[D / 16];
-        read_k(c, kf);
-        f32x16 sv = s_of(kf);
-        mask(sv, kval[slot(c)]);
-        bool rs;
-        bf16x8 pc[2];
-        const float alpha = softmax(sv, pc, &rs);
-        if (rs) scale_o(alpha);
-        bf16x8 vf[D / 32][2];
-        read_v(c, vf);
-        pv(vf, pc);
-      }
-    };
-    issue();  // window 0
-    issue();  // window 1
-    wait_chunks<LY::LPC>(sidx + 4 < nch ? 1 : 0);
-    __syncthreads();  // window 0 landed
-#pragma unroll 1
-    for (int w = 0; w + 1 < nbar; ++w) {
-      tile4(4 * w + sidx);
-      wait_chunks<LY::LPC>(0);
-      __syncthreads();  // window w + 1 landed
-      issue();          // window w + 2, into the slots of chunks 4w - 1 .. 4w + 2
-    }
-    tile4(4 * (nbar - 1) + sidx);
-  }
-
-  // tile 4: the Y waves' partial states merge in LDS (the ring is free once every
-  // wave is past its walk)
-  float* mg = reinterpret_cast<float*>(smem_raw);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (is_y && sidx > 0 && rows_live) {
-    float* dst = mg + (sidx - 1) * (LY::MERGE_FLOATS * 64);
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[(t * 16 + r) * 64 + lane] = o[t][r];
-    dst[(D / 32 * 16) * 64 + lane] = m;
-    dst[(D / 32 * 16 + 1) * 64 + lane] = l;
-  }
-  __syncthreads();
-  if (is_y && sidx > 0) return;
-  if (is_y && rows_live) {
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k) {
-      const float* src = mg + k * (LY::MERGE_FLOATS * 64);
-      const float mB = src[(D / 32 * 16) * 64 + lane];
-      const float lB = src[(D / 32 * 16 + 1) * 64 + lane];
-      const float mm = fmaxf(m, mB);
-      const bool none = mm == -INFINITY;
-      const float aA = none ? 0.0f : __builtin_amdgcn_exp2f(m - mm);
-      const float aB = none ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
-#pragma unroll
-      for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][r] = o[t][r] * aA + src[(t * 16 + r) * 64 + lane] * aB;
-      l = l * aA + lB * aB;
-      m = mm;
-    }
-  }
-  if (tile >= T) return;
-  {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l),
-                                                     false, false);
-    l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  }
-  const int qs = q0 + r32;
-  if (RASTER ? qs < n_i : qs < g.BS) {
-    const bool real = qs < n_i;
-    const float inv = (real && l > 0.0f) ? 1.0f / l : 0.0f;
-    const int64_t orow = real ? q_row(qs) : head_row + int64_t(i) * g.BS + qs;
-    __bf16* dst = ob + orow * D + 4 * half;
-#pragma unroll
-    for (int t = 0; t < D / 32; ++t)
-#pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __bf16(o[t][4 * rq + e] * inv);
-        *reinterpret_cast<bf16x4*>(dst + 32 * t + 8 * rq) = v;
-      }
-    if (lse && real && half == 0)
-      lse[orow] = l > 0.0f ? (m + log2f(l)) * 0.69314718055994530942f : -INFINITY;
-  }
-}
-
-template <int D, int T, bool RASTER, bool MULTI>
-hipError_t launch_sw(const DevGeom& g, const void* qb, const void* kb, const void* vb,
-                     const int* counts, const int* indices, float scale_log2, void* ob,
-                     float* lse, hipStream_t s, const MultiTable* tab, const int* order,
-                     int nb_max) {
-  {  // the ring and the kept list exceed the 64 KB default
-    const hipError_t e = ensure_dynamic_lds(
-        reinterpret_cast<const void*>(&attn_sw_kernel<D, T, RASTER, MULTI>), kSwLds);
-    if (e != hipSuccess) return e;
-  }
-  const size_t lds = size_t(SwLayout<D>::LIST_OFF) + size_t(nb_max) * sizeof(int);
-  const uint4* q4 = static_cast<const uint4*>(qb);
-  const char* k1 = static_cast<const char*>(kb);
-  const char* v1 = static_cast<const char*>(vb);
-  __bf16* o2 = static_cast<__bf16*>(ob);
-  if constexpr (MULTI) {
-    const int64_t items = int64_t(g.B) * tab->items_per_batch;
-    attn_sw_kernel<D, T, RASTER, MULTI><<<dim3(unsigned(items)), 64 * kSwWaves, lds, s>>>(
-        g, q4, k1, v1, nullptr, nullptr, scale_log2, o2, lse, order, *tab);
-  } else {
-    const int64_t items = int64_t(g.B) * g.H * ((g.NB + 7) / 8) * 8;  // see the XCD mapping
-    attn_sw_kernel<D, T, RASTER, MULTI><<<dim3(unsigned(items)), 64 * kSwWaves, lds, s>>>(
-        g, q4, k1, v1, counts, indices, scale_log2, o2, lse, order, NoTable{});
-  }
-  return hipGetLastError();
-}
-
-template <int D, int W, bool LD, bool RASTER, bool MULTI>
-hipError_t launch_dw(const DevGeom& g, const void* qb, const void* kb, const void* vb,
-                     const int* counts, const int* indices, float scale_log2, void* ob, float* lse,
-                     hipStream_t s, const MultiTable* tab = nullptr, const int* order = nullptr) {
-  {  // allow the kept-list LDS beyond the 64 KB default
-    const hipError_t e = ensure_dynamic_lds(
-        reinterpret_cast<const void*>(&attn_kernel<D, W, LD, RASTER, MULTI>),
-        int(kMaxAttnNB * sizeof(int)));
-    if (e != hipSuccess) return e;
-  }
-  const uint4* q4 = static_cast<const uint4*>(qb);
-  const char* k1 = static_cast<const char*>(kb);
-  const char* v1 = static_cast<const char*>(vb);
-  __bf16* o2 = static_cast<__bf16*>(ob);
-  if constexpr (MULTI) {
-    int nb_max = 0;
-    for (int k = 0; k < tab->n_heads; ++k) nb_max = max(nb_max, tab->geo[tab->head[k].geom].NB);
-    const int64_t items = int64_t(g.B) * tab->items_per_batch;
-    attn_kernel<D, W, LD, RASTER, MULTI><<<dim3(unsigned(items)), 64 * (W + LD),
-                                           size_t(nb_max) * sizeof(int), s>>>(
-        g, q4, k1, v1, nullptr, nullptr, scale_log2, o2, lse, order, *tab);
-  } else {
-    const int64_t items = int64_t(g.B) * g.H * ((g.NB + 7) / 8) * 8;  // see the XCD mapping
-    attn_kernel<D, W, LD, RASTER, MULTI><<<dim3(unsigned(items)), 64 * (W + LD),
-                                           size_t(g.NB) * sizeof(int), s>>>(
-        g, q4, k1, v1, counts, indices, scale_log2, o2, lse, order, NoTable{});
+    kernel<<<dim3(unsigned(items)), threads, lds, s>>>(g, q4, k1, v1, counts, indices, scale_log2,
+                                                       o2, lse, order, NoTable{});
   }
   return hipGetLastError();
 }
@@ -1548,35 +964,68 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
                     const int* counts, const int* indices, float scale_log2, void* ob, float* lse,
                     hipStream_t s, const MultiTable* tab = nullptr, const int* order = nullptr) {
   int nb_max = g.NB;
+  int64_t items = int64_t(g.B) * g.H * g.NB;
   if constexpr (MULTI) {
     nb_max = 0;
     for (int k = 0; k < tab->n_heads; ++k) nb_max = max(nb_max, tab->geo[tab->head[k].geom].NB);
+    items = int64_t(g.B) * tab->items_per_batch;
   }
-  // 5 row tiles: the software-pipelined kernel when its ring and the kept list fit
-  // the LDS (4-tile blocks stay on attn_kernel: with one pipelined wave per tile
-  // and idle DMA waves the sw form was 15% slower there)
-  if constexpr (D == 128) {
-    if ((g.BS + 31) / 32 == kSwTiles &&
-        size_t(SwLayout<D>::LIST_OFF) + size_t(nb_max) * sizeof(int) <= size_t(kSwLds))
-      return launch_sw<D, kSwTiles, RASTER, MULTI>(g, qb, kb, vb, counts, indices, scale_log2, ob,
-                                                   lse, s, tab, order, nb_max);
+  auto run = [&](auto kernel, int threads, size_t lds, int max_lds) {
+    return launch_items<MULTI>(kernel, threads, lds, max_lds, g, qb, kb, vb, counts, indices,
+                               scale_log2, ob, lse, s, tab, order);
+  };
+  auto five = [&](auto kernel) {
+    return run(kernel, 512, FiveTileLayout<D>::BYTES, FiveTileLayout<D>::BYTES);
+  };
+  auto loader = [&](auto kernel, int w) {
+    return run(kernel, 64 * (w + 1), size_t(nb_max) * sizeof(int), int(kMaxAttnNB * sizeof(int)));
+  };
+  auto walk = [&](auto kernel, auto layout, int w) {
+    return run(kernel, 64 * w, size_t(layout.BYTES), int(layout.BYTES));
+  };
+  // the walk over concatenated keys where it saves chunks (WalkCursor)
+  bool stream = false;
+  if constexpr (MULTI) {
+    for (int k = 0; k < tab->n_heads; ++k) stream |= saves_chunks(tab->geo[tab->head[k].geom]);
+  } else {
+    stream = saves_chunks(g);
   }
-  // otherwise the paired kernel for 5 row tiles when its ring and the kept list fit
-  if ((g.BS + 31) / 32 == kPairTiles &&
-      size_t(PPLayout<D>::LIST_OFF) + size_t(nb_max) * sizeof(int) <= size_t(kPairLds))
-    return launch_pp<D, kPairTiles, RASTER, MULTI>(g, qb, kb, vb, counts, indices, scale_log2, ob,
-                                                   lse, s, tab, order, nb_max);
-#define SPADE_ATTN_CASE(w, ld)                                                                  \
-  case w:                                                                                       \
-    return launch_dw<D, w, ld, RASTER, MULTI>(g, qb, kb, vb, counts, indices, scale_log2, ob, \
-                                              lse, s, tab, order);
-  // loader wave unless it would cost a workgroup per CU (4 or 6 compute waves)
+#define SPADE_ATTN_WALK(w)                                                             \
+  (stream ? walk(attn_kernel<D, w, RASTER, MULTI, true>, WalkLayout<D, w>{}, w)        \
+          : walk(attn_kernel<D, w, RASTER, MULTI, false>, WalkLayout<D, w>{}, w))
   switch ((g.BS + 31) / 32) {
-    SPADE_ATTN_CASE(1, true) SPADE_ATTN_CASE(2, true) SPADE_ATTN_CASE(3, true)
-    SPADE_ATTN_CASE(4, false) SPADE_ATTN_CASE(5, true) SPADE_ATTN_CASE(6, false)
-    SPADE_ATTN_CASE(7, true) SPADE_ATTN_CASE(8, true)
+    case 1: return SPADE_ATTN_WALK(1);
+    case 2:
+      // 64-token blocks at d = 128 load 16 KB per 64 query rows and chunk. Launches of many
+      // rounds are bound by those loads, which a wave of its own keeps further ahead (4.84
+      // against 5.06 ms at 11520 items); shorter ones by a work item's latency (0.45 against
+      // 0.58 ms at 2016 items).
+      if constexpr (D == 128) {
+        if (items >= kLoaderItems) return loader(attn_loader_kernel<D, 2, RASTER, MULTI>, 2);
+      }
+      return SPADE_ATTN_WALK(2);
+    case 3: return SPADE_ATTN_WALK(3);
+    case 4: return SPADE_ATTN_WALK(4);
+    case 5:
+      if constexpr (D == 64) {
+        return five(attn_pp_kernel<D, 5, RASTER, MULTI>);
+      } else {
+        if (nb_max <= kSwBlocks) return five(attn_sw_kernel<D, 5, RASTER, MULTI>);
+        if (nb_max <= kPpBlocks) return five(attn_pp_kernel<D, 5, RASTER, MULTI>);
+        return five(attn_kernel<D, 5, RASTER, MULTI, true>);
+      }
+    case 6: return SPADE_ATTN_WALK(6);
+    case 7:
+      // at d = 64 seven waves of up to 128 registers plus a loader leave room for two
+      // workgroups per CU, the walk's seven of 157 for one: 3.23 against 3.47 ms (57600
+      // tokens, 12 heads)
+      if constexpr (D == 64)
+        return loader(attn_loader_kernel<D, 7, RASTER, MULTI>, 7);
+      else
+        return SPADE_ATTN_WALK(7);
+    case 8: return SPADE_ATTN_WALK(8);
   }
-#undef SPADE_ATTN_CASE
+#undef SPADE_ATTN_WALK
   return hipErrorInvalidValue;
 }
 
