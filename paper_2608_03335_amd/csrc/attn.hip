@@ -58,7 +58,7 @@ struct Item {
   DevGeom g;
   int64_t bh;
   int i;
-  const int* cnt_src;
+  int cnt;  // its kept blocks, clamped to [0, NB]
   const int* list_src;
 };
 
@@ -67,18 +67,30 @@ struct Item {
 // XCD's CUs then start its rows heaviest first: rows of similar length walk the key
 // blocks at a similar pace, so the K/V blocks they share meet in the XCD's L2, and long
 // rows do not form the tail. Any order is correct: each row is one work item.
-__device__ __forceinline__ int heavy_first(const int* __restrict__ c, int n, int r, int NB) {
+// A radix selection over the window's counts, one ballot per bit: every wave of a workgroup
+// does it before its first load, and ranking all 64 against each other took three times
+// as long. *count: the row's kept blocks, clamped to [0, NB].
+__device__ __forceinline__ int heavy_first(const int* __restrict__ c, int n, int r, int NB,
+                                           int* count) {
   const int lane = int(threadIdx.x & 63);
   const int w0 = r & ~63, wn = min(64, n - w0);
-  const int cl = min(max(c[w0 + min(lane, wn - 1)], 0), NB);  // lanes past the window re-read
-  const int key = lane < wn ? cl : -1;
-  int rank = 0;
-  for (int t = 0; t < wn; ++t) {
-    const int kt = __builtin_amdgcn_readlane(key, t);
-    rank += (kt > key || (kt == key && t < lane)) ? 1 : 0;
+  const int cl = min(max(c[w0 + min(lane, wn - 1)], 0), NB);
+  uint64_t cand = wn == 64 ? ~uint64_t(0) : (uint64_t(1) << wn) - 1;
+  int need = r - w0;  // rank within the candidates
+  for (int b = 31 - __builtin_clz(uint32_t(NB)); b >= 0; --b) {
+    const uint64_t ones = cand & __ballot((cl >> b) & 1);
+    const int n1 = __popcll(ones);
+    const bool in = need < n1;
+    cand = in ? ones : cand & ~ones;
+    need -= in ? 0 : n1;
   }
-  const uint64_t hit = __ballot(lane < wn && rank == r - w0);
-  return w0 + __builtin_amdgcn_readfirstlane(int(__builtin_ctzll(hit)));
+  // equal counts: the candidate of index `need`
+  const int at = __builtin_amdgcn_mbcnt_hi(uint32_t(cand >> 32),
+                                           __builtin_amdgcn_mbcnt_lo(uint32_t(cand), 0));
+  const uint64_t hit = __ballot(at == need) & cand;
+  const int row = __builtin_amdgcn_readfirstlane(int(__builtin_ctzll(hit)));
+  *count = __builtin_amdgcn_readlane(cl, row);
+  return w0 + row;
 }
 
 template <bool MULTI, class Tab>
@@ -116,9 +128,8 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
       return it;
     }
     const int* hc = mh.counts + int64_t(b) * mh.counts_bstride;
-    it.i = lo + heavy_first(hc + lo, rows, r, it.g.NB);
+    it.i = lo + heavy_first(hc + lo, rows, r, it.g.NB, &it.cnt);
     it.bh = int64_t(b) * it.g.H + mh.h;
-    it.cnt_src = hc + it.i;
     it.list_src = mh.indices + int64_t(b) * mh.indices_bstride + int64_t(it.i) * it.g.NB;
   } else {
     const DevGeom& g = it.g;
@@ -132,8 +143,7 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
       it.i = -1;
       return it;
     }
-    it.i = lo + heavy_first(counts + it.bh * g.NB + lo, rows, r, g.NB);
-    it.cnt_src = counts + it.bh * g.NB + it.i;
+    it.i = lo + heavy_first(counts + it.bh * g.NB + lo, rows, r, g.NB, &it.cnt);
     it.list_src = indices + (it.bh * g.NB + it.i) * int64_t(g.NB);
   }
   return it;
@@ -189,10 +199,11 @@ __device__ __forceinline__ void row_tile_walk(const Item& it, const uint4* __res
   const bool rows_live = q0 < e_i.n;
   const int64_t head_row = RASTER ? it.bh * g.N : it.bh * g.NB * int64_t(g.BS);
   const int64_t first_row = head_row + int64_t(it.i) * g.BS;  // blocked layout
+  const int cnt = it.cnt;
+  const int j0 = tid < min(cnt, LY::SEG) ? it.list_src[tid] : -1;  // in flight beside the tables
   TileState<D> x;
   load_q<D, RASTER>(g, e_i, qb, head_row, first_row, q0, x.qf);
   clear_tile(x);
-  const int cnt = min(max(*it.cnt_src, 0), g.NB);
   slot_tables<D, W, RASTER>(g, (lds_int*)(smem_raw + LY::TAB_OFF), tid, NT);
 
   const FragAddr fr(lane);
@@ -208,7 +219,7 @@ __device__ __forceinline__ void row_tile_walk(const Item& it, const uint4* __res
   for (int seg = 0; seg < cnt; seg += LY::SEG) {
     const int ns = min(cnt - seg, LY::SEG);
     if (seg) __syncthreads();
-    const Staged st = stage_list<D, RASTER, STREAM>(g, it.list_src + seg, ns, list, tid, lane, NT);
+    const Staged st = stage_list<D, RASTER, STREAM>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT);
     const int n = st.chunks;
     if (n == 0) continue;
     WalkCursor<LY::TAB_OFF, W, STREAM> cur(list, ns, st.stream);
@@ -345,9 +356,37 @@ struct FiveTileLayout {
   static constexpr int LIST_OFF = KV_OFF + 64;
   static constexpr int SEG = 512;  // kept-list entries staged at a time
   static constexpr int BYTES = LIST_OFF + (SEG + 1) * 8;
-  static constexpr int MERGE_FLOATS = D / 32 * 16 + 2;  // per lane: O, m, l
   static_assert(BYTES <= 160 * 1024, "one CU's LDS");
 };
+
+// Stores accumulators quarter * SH .. of a tile (the merged fifth tile), see store_tile.
+template <int D, bool RASTER>
+__device__ __forceinline__ void store_quarter(const DevGeom& g, const BlockExt& e, int quarter,
+                                              const float* acc, float m, float l, int q0,
+                                              int64_t first_row, int64_t head_row, __bf16* ob,
+                                              float* lse) {
+  constexpr int SH = D / 8;
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false,
+                                                   false);
+  l = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  const int ln = lane_now();
+  const int qs = q0 + (ln & 31), half = ln >> 5;
+  const bool real = qs < e.n;
+  if (RASTER ? real : qs < g.BS) {
+    const float inv = (real && l > 0.0f) ? 1.0f / l : 0.0f;
+    const int64_t row = RASTER ? head_row + ext_token(g, e, qs) : first_row + qs;
+    __bf16* dst = ob + row * D + quarter * (SH * 2) + 4 * half;
+#pragma unroll
+    for (int r = 0; r < SH; r += 4) {
+      bf16x4 v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = __bf16(acc ? acc[r + k] * inv : 0.0f);
+      *reinterpret_cast<bf16x4*>(dst + 2 * r) = v;
+    }
+    if (lse && real && half == 0 && quarter == 0)
+      lse[row] = l > 0.0f ? (m + log2f(l)) * kLn2 : -INFINITY;
+  }
+}
 
 template <int D, bool RASTER, bool MULTI>
 __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __restrict__ qb,
@@ -371,7 +410,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
   const bool rows_live = q0 < e_i.n;
   const int64_t head_row = RASTER ? it.bh * g.N : it.bh * g.NB * int64_t(g.BS);
   const int64_t first_row = head_row + int64_t(it.i) * g.BS;  // blocked layout
-  const int cnt = min(max(*it.cnt_src, 0), g.NB);
+  const int cnt = it.cnt;
+  const int j0 = tid < min(cnt, LY::SEG) ? it.list_src[tid] : -1;  // in flight beside the tables
   slot_tables<D, LY::T, RASTER>(g, (lds_int*)(smem_raw + LY::TAB_OFF), tid, NT);
   const FragAddr fr(lane);
 
@@ -383,7 +423,7 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
     for (int seg = 0; seg < cnt; seg += LY::SEG) {
       const int ns = min(cnt - seg, LY::SEG);
       if (seg) __syncthreads();
-      const int n = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, list, tid, lane, NT).chunks;
+      const int n = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT).chunks;
       if (n == 0) continue;
       // P of "chunk -1" is zero; its V slot must hold finite values
       for (int e = tid; e < LY::TILE / 16; e += 256)
@@ -436,8 +476,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
       finish_chunk<D>(x, pA, lds, fr.v + vs_prev);
     }
     __syncthreads();  // every walk is done (the merge overwrites the rings)
-    __syncthreads();
     store_tile<D, RASTER>(g, e_i, x, q0, head_row, first_row, ob, lse);
+    __syncthreads();
     return;
   }
 
@@ -453,7 +493,7 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
   for (int seg = 0; seg < cnt; seg += LY::SEG) {
     const int ns = min(cnt - seg, LY::SEG);
     if (seg) __syncthreads();
-    const Staged st = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, list, tid, lane, NT);
+    const Staged st = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT);
     const int n = st.chunks;
     if (n == 0) continue;
     __builtin_amdgcn_s_waitcnt(0);  // Q and list loads are done: only DMA is counted below
@@ -504,40 +544,42 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
     compute(4 * nb + sidx);
   }
 
-  // tile 4: the Y waves' partial states merge in LDS
-  float* mg = reinterpret_cast<float*>(smem_raw);
+  // tile 4: the Y waves' partial states merge in LDS, each wave a quarter of the columns,
+  // summed in the order Y_0 .. Y_3 (one wave merging all of them kept the CU 2k cycles
+  // longer)
+  constexpr int SH = KV::DT * 16 / 4;  // accumulators per quarter
+  float* const ml = reinterpret_cast<float*>(smem_raw);  // [wave][lane][2]
+  float* const part = ml + 4 * 128;                      // [quarter][wave][SH][lane]
   __syncthreads();
-  if (sidx > 0 && rows_live) {
-    float* dst = mg + (sidx - 1) * (LY::MERGE_FLOATS * 64);
-#pragma unroll
-    for (int t = 0; t < KV::DT; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[(t * 16 + r) * 64 + lane] = x.o[t][r];
-    dst[(KV::DT * 16) * 64 + lane] = x.m;
-    dst[(KV::DT * 16 + 1) * 64 + lane] = x.l;
-  }
-  __syncthreads();
-  if (sidx > 0) return;
   if (rows_live) {
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k) {
-      const float* src = mg + k * (LY::MERGE_FLOATS * 64);
-      const float mB = src[(KV::DT * 16) * 64 + lane];
-      const float lB = src[(KV::DT * 16 + 1) * 64 + lane];
-      const float mm = fmaxf(x.m, mB);
-      const bool none = mm == -INFINITY;
-      const float aA = none ? 0.0f : __builtin_amdgcn_exp2f(x.m - mm);
-      const float aB = none ? 0.0f : __builtin_amdgcn_exp2f(mB - mm);
+    ml[(sidx * 64 + lane) * 2] = x.m;
+    ml[(sidx * 64 + lane) * 2 + 1] = x.l;
 #pragma unroll
-      for (int t = 0; t < KV::DT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          x.o[t][r] = x.o[t][r] * aA + src[(t * 16 + r) * 64 + lane] * aB;
-      x.l = x.l * aA + lB * aB;
-      x.m = mm;
-    }
+    for (int r = 0; r < KV::DT * 16; ++r)
+      part[((r / SH * 4 + sidx) * SH + r % SH) * 64 + lane] = x.o[r / 16][r % 16];
   }
-  store_tile<D, RASTER>(g, e_i, x, q0, head_row, first_row, ob, lse);
+  __syncthreads();
+  if (!rows_live) {
+    store_quarter<D, RASTER>(g, e_i, sidx, nullptr, 0.0f, 0.0f, q0, first_row, head_row, ob, lse);
+    return;
+  }
+  float f[4], mm = -INFINITY, l = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) mm = fmaxf(mm, ml[(k * 64 + lane) * 2]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    f[k] = mm == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ml[(k * 64 + lane) * 2] - mm);
+    l += ml[(k * 64 + lane) * 2 + 1] * f[k];
+  }
+  float acc[SH];
+#pragma unroll
+  for (int r = 0; r < SH; ++r) {
+    acc[r] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      acc[r] += part[((sidx * 4 + k) * SH + r) * 64 + lane] * f[k];
+  }
+  store_quarter<D, RASTER>(g, e_i, sidx, acc, mm, l, q0, first_row, head_row, ob, lse);
 }
 
 // Kernels. MULTI (raster only): one launch over heads with different blockings; the work
@@ -722,7 +764,6 @@ __global__ void __launch_bounds__(64 * (W + 1))
   const DevGeom g = it.g;
   const int64_t bh = it.bh;
   const int i = it.i;
-  const int* const cnt_src = it.cnt_src;
   const int* const list_src = it.list_src;
   const BlockExt e_i = block_ext(g, i);
   const int n_i = e_i.n;
@@ -751,7 +792,7 @@ __global__ void __launch_bounds__(64 * (W + 1))
     }
   }
 
-  const int cnt = min(max(*cnt_src, 0), g.NB);
+  const int cnt = it.cnt;
   for (int e = threadIdx.x; e < cnt; e += 64 * (W + 1)) list[e] = list_src[e];
   if (RASTER) {
     for (int sl = threadIdx.x; sl < g.BS; sl += 64 * (W + 1)) {

@@ -146,12 +146,41 @@ __device__ __forceinline__ void slot_tables(const DevGeom& g, lds_int* rel, int 
     for (int e = tid; e < 4 * T * 32; e += nt) {
       const int v = e / (T * 32), sl = e % (T * 32);
       const int ew = (v & 1) ? ew_r : g.bw, eh = (v & 2) ? eh_r : g.bh;
-      const int q = sl / ew;
-      rel[e] = (((q / eh) * g.Hs + q % eh) * g.Ws + sl % ew) * KvTile<D>::ROW;
+      // float quotients, exact below 2^8 (block_slot_token)
+      const int q = int((float(sl) + 0.5f) * __builtin_amdgcn_rcpf(float(ew)));
+      const int dt = int((float(q) + 0.5f) * __builtin_amdgcn_rcpf(float(eh)));
+      rel[e] = ((dt * g.Hs + q - dt * eh) * g.Ws + sl - q * ew) * KvTile<D>::ROW;
     }
   } else {
     for (int e = tid; e < T * 32; e += nt) rel[e] = e * KvTile<D>::ROW;
   }
+}
+
+// block_ext with float quotients, for j < 2^14: (j + 0.5) / d lies 0.5 / d from an
+// integer and comes out within 2^-9 / d of it.
+__device__ __forceinline__ BlockExt list_block_ext(const DevGeom& g, int j) {
+  const int r = int((float(j) + 0.5f) * __builtin_amdgcn_rcpf(float(g.nW)));
+  const int tb = int((float(r) + 0.5f) * __builtin_amdgcn_rcpf(float(g.nH)));
+  BlockExt e;
+  e.t0 = tb * g.bt;
+  e.y0 = (r - tb * g.nH) * g.bh;
+  e.x0 = (j - r * g.nW) * g.bw;
+  e.et = min(g.bt, g.T - e.t0);
+  e.eh = min(g.bh, g.Hs - e.y0);
+  e.ew = min(g.bw, g.Ws - e.x0);
+  e.n = e.et * e.eh * e.ew;
+  return e;
+}
+
+// Sum over the wave by DPP (quads, half rows, rows) and the four row totals: a tenth of the
+// time of six dependent LDS shuffles.
+__device__ __forceinline__ int wave_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);   // quad_perm [1,0,3,2]
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);   // quad_perm [2,3,0,1]
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);  // row_half_mirror
+  v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);  // row_mirror
+  return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
+         __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
 // A staged part of the kept list: its chunks, and whether they run across block boundaries.
@@ -165,15 +194,16 @@ struct Staged {
 // chunk, and every block has at least kChunk keys (so a chunk spans at most two of them),
 // the walk runs over the concatenated keys and only the last chunk is partly empty: 10%
 // fewer chunks for blocks of 144 keys, 6% for 120 (12 heads of 32760 tokens, every block
-// kept: 8.40 -> 7.60 ms). Every wave returns the same result.
+// kept: 8.40 -> 7.60 ms). j0: the entry of index tid, loaded earlier (-2: not loaded). Every
+// wave returns the same result.
 template <int D, bool RASTER, bool STREAM>
 __device__ __forceinline__ Staged stage_list(const DevGeom& g, const int* src, int ns,
-                                             lds_int* list, int tid, int lane, int nt) {
+                                             int j0, lds_int* list, int tid, int lane, int nt) {
   for (int e = tid; e < ns; e += nt) {
-    const int j = src[e];
+    const int j = e == tid && j0 != -2 ? j0 : src[e];
     int2 ent = make_int2(0, 0);
     if (j >= 0 && j < g.NB) {
-      const BlockExt be = block_ext(g, j);
+      const BlockExt be = list_block_ext(g, j);
       const int var = RASTER ? (be.ew != g.bw ? 1 : 0) | (be.eh != g.bh ? 2 : 0) : 0;
       ent = make_int2((RASTER ? int(block_origin(g, be)) : j * g.BS) * KvTile<D>::ROW,
                       be.n | (var << 16));
@@ -191,13 +221,10 @@ __device__ __forceinline__ Staged stage_list(const DevGeom& g, const int* src, i
     small = small || n < kChunk;
     part = part || n % kChunk != 0;
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    keys += __shfl_xor(keys, off);
-    apart += __shfl_xor(apart, off);
-  }
+  keys = wave_sum(keys);
+  apart = wave_sum(apart);
   const bool stream = STREAM && __ballot(small) == 0 && __ballot(part) != 0;
-  return {__builtin_amdgcn_readfirstlane(stream ? (keys + kChunk - 1) / kChunk : apart), stream};
+  return {stream ? (keys + kChunk - 1) / kChunk : apart, stream};
 }
 
 // Position of a chunk in a staged list: it starts at slot c0 of the current entry (n real
