@@ -276,12 +276,12 @@ __device__ void intra_topk_marks(const DevGeom& g, const double* sics, int k, in
 }
 
 // Rows of up to 512 blocks (SM <= 8) fit in 128 VGPRs with the DSA2 estimator (up to
-// four waves per SIMD) and in 168 with the mean estimator, whose score phase holds two
-// key tiles (three waves per SIMD); the LDS (12 score rows + histograms) allows three
+// four waves per SIMD) and in 168 with the others, whose score phase holds two key tiles
+// or two halves of extremes (three waves per SIMD); the LDS (12 score rows + histograms) allows three
 // workgroups per CU either way.
 template <int D, int EST, int SM>
 __global__ void __launch_bounds__(kThreads)
-    __attribute__((amdgpu_waves_per_eu(SM <= 8 && EST != kEstDsa ? (EST == kEstMean ? 3 : 4) : 1)))
+    __attribute__((amdgpu_waves_per_eu(SM <= 8 ? (EST == kEstDsa2 ? 4 : 3) : 1)))
     select_kernel(DevGeom g, SelectSpec p) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int NB = g.NB;
@@ -364,91 +364,124 @@ __global__ void __launch_bounds__(kThreads)
         tile(kB, jt1);
       }
     } else {
-    double qa[2 * KQ];
-    {
-      const int row = i0 + r16;
-      const int64_t ro = int64_t(min(row, NB - 1)) * D;
-      const double2* p0 = reinterpret_cast<const double2*>(q0 + ro) + g4;
-      const double2* p1 = EST == kEstDsa ? reinterpret_cast<const double2*>(p.q1 + bh * NB * D + ro) + g4
-                                         : nullptr;
-#pragma unroll
-      for (int kq = 0; kq < KQ; ++kq) {
-        double2 v = p0[4 * kq];
-        if (EST == kEstDsa) {
-          const double2 u = p1[4 * kq];
-          v.x = (v.x + u.x) * 0.5;
-          v.y = (v.y + u.y) * 0.5;
-        }
-        qa[2 * kq] = row < NB ? v.x : 0.0;
-        qa[2 * kq + 1] = row < NB ? v.y : 0.0;
+      // DSA: A = q~ = (qmax + qmin)/2 (staged as above) against B = k_c, then |q~| against
+      // k_r. Half a key tile's extremes (64 registers) are in flight while the other half is
+      // contracted; loading each tile when it was needed left the contraction waiting:
+      // 122 -> 104 us at 24 heads of 360 blocks.
+      constexpr int HQ = KQ / 2;
+      double* qs = reinterpret_cast<double*>(hist_w);  // [16][kQsStride]
+      for (int e = threadIdx.x; e < 16 * D; e += kThreads) {
+        const int r = e / D, row = i0 + r;
+        const int64_t at = int64_t(row) * D + e % D;
+        qs[r * kQsStride<D> + e % D] =
+            (r < kRows && row < NB) ? (q0[at] + p.q1[bh * NB * D + at]) * 0.5 : 0.0;
       }
-    }
-    for (int jt = wave; jt < ntiles; jt += kWaves) {
-      const int col = jt * 16 + r16;
-      const int64_t co = int64_t(min(col, NB - 1)) * D;
-      const double2* pk = reinterpret_cast<const double2*>(k0 + co) + g4;
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      if (EST == kEstMean) {
+      __syncthreads();
+      const double* const k1 = p.k1 + bh * NB * D;
+      auto load_k = [&](double2 (&x)[HQ], double2 (&n)[HQ], int jt, int h) {
+        const int64_t co = int64_t(min(jt * 16 + r16, NB - 1)) * D;
+        const double2* px = reinterpret_cast<const double2*>(k0 + co) + g4 + 4 * HQ * h;
+        const double2* pn = reinterpret_cast<const double2*>(k1 + co) + g4 + 4 * HQ * h;
 #pragma unroll
-        for (int kq = 0; kq < KQ; ++kq) {
-          const double2 kv = pk[4 * kq];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[2 * kq], kv.x, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[2 * kq + 1], kv.y, acc, 0, 0, 0);
+        for (int kq = 0; kq < HQ; ++kq) {
+          x[kq] = px[4 * kq];
+          n[kq] = pn[4 * kq];
         }
-      } else {
-        const double2* pn = reinterpret_cast<const double2*>(p.k1 + bh * NB * D + co) + g4;
+      };
+      auto half = [&](f64x4 acc, const double2 (&x)[HQ], const double2 (&n)[HQ], int h) {
+        const double* qrow = qs + r16 * kQsStride<D> + 2 * g4 + 8 * HQ * h;
 #pragma unroll
-        for (int kq = 0; kq < KQ; ++kq) {
-          const double2 a = pk[4 * kq], b = pn[4 * kq];
+        for (int kq = 0; kq < HQ; ++kq) {
+          const double2 q = *reinterpret_cast<const double2*>(qrow + 8 * kq);
+          const double2 a = x[kq], b = n[kq];
           const double cx = (a.x + b.x) * 0.5, cy = (a.y + b.y) * 0.5;  // centre (exact)
           const double rx = (a.x - b.x) * 0.5, ry = (a.y - b.y) * 0.5;  // half width (exact)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[2 * kq], cx, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[2 * kq + 1], cy, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fabs(qa[2 * kq]), rx, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fabs(qa[2 * kq + 1]), ry, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(q.x, cx, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(q.y, cy, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fabs(q.x), rx, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fabs(q.y), ry, acc, 0, 0, 0);
         }
-      }
-      if (col < NB) {
+        return acc;
+      };
+      double2 xA[HQ], nA[HQ], xB[HQ], nB[HQ];
+      if (wave < ntiles) load_k(xA, nA, wave, 0);
+      for (int jt = wave; jt < ntiles; jt += kWaves) {
+        load_k(xB, nB, jt, 1);
+        f64x4 acc = half(f64x4{0.0, 0.0, 0.0, 0.0}, xA, nA, 0);
+        if (jt + kWaves < ntiles) load_k(xA, nA, jt + kWaves, 0);
+        acc = half(acc, xB, nB, 1);
+        const int col = jt * 16 + r16;
+        if (col < NB) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {  // acc[r] = S[4r + g4][r16]
-          const int rr = 4 * r + g4;  // tile rows past kRows belong to the next item
-          const double s = acc[r] * p.scale + 0.0;  // + 0.0 folds -0 into +0
-          if (rr < kRows) sc[rr * NB + col] = s;
-          if (p.scores && rr < kRows && i0 + rr < NB) p.scores[(bh * NB + i0 + rr) * NB + col] = s;
+          for (int r = 0; r < 4; ++r) {  // acc[r] = S[4r + g4][r16]
+            const int rr = 4 * r + g4;  // tile rows past kRows belong to the next item
+            const double v = acc[r] * p.scale + 0.0;  // + 0.0 folds -0 into +0
+            if (rr < kRows) sc[rr * NB + col] = v;
+            if (p.scores && rr < kRows && i0 + rr < NB) p.scores[(bh * NB + i0 + rr) * NB + col] = v;
+          }
         }
       }
-    }
     }
   } else {
-    // DSA2 on the VALU: lane (r16, g4) scores column jt*16 + r16 against rows
-    // 4r + g4, summing channels in order.
+    // DSA2 on the VALU (8 fp64 operations per row, column and channel, the channels of a
+    // score summed in order): a lane owns one key block for all rows of the item, so a
+    // key's extremes are loaded once for twelve rows, 64 bytes at a time and one step
+    // ahead, and the query rows come from LDS as broadcasts. With a lane on one column and
+    // four rows the kernel spent its time on loads (10 per two channels): 133 -> 77 us
+    // at 8 heads of 252 blocks.
+    double2* const qs = reinterpret_cast<double2*>(hist_w);  // [row][D / 2][max, min]
     const double* q1 = p.q1 + bh * NB * D;
     const double* k1 = p.k1 + bh * NB * D;
-    for (int jt = wave; jt < ntiles; jt += kWaves) {
-      const int col = jt * 16 + r16;
-      const int64_t co = int64_t(min(col, NB - 1)) * D;
-      double acc[4] = {0.0, 0.0, 0.0, 0.0};
-      int64_t ro[4];
+    for (int e = threadIdx.x; e < kRows * D / 2; e += kThreads) {
+      const int r = e / (D / 2), c = e % (D / 2);
+      const int64_t ro = int64_t(min(i0 + r, NB - 1)) * (D / 2) + c;
+      qs[2 * e] = reinterpret_cast<const double2*>(q0)[ro];
+      qs[2 * e + 1] = reinterpret_cast<const double2*>(q1)[ro];
+    }
+    __syncthreads();
+    constexpr int KP = 4;  // channel pairs per step
+    for (int j0 = wave * 64; j0 < NB; j0 += 64 * kWaves) {
+      const int col = j0 + lane;
+      const int64_t co = int64_t(min(col, NB - 1)) * (D / 2);
+      const double2* kx = reinterpret_cast<const double2*>(k0) + co;
+      const double2* kn = reinterpret_cast<const double2*>(k1) + co;
+      double acc[kRows];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ro[r] = int64_t(min(i0 + 4 * r + g4, NB - 1)) * D;
-      for (int c = 0; c < D; c += 2) {
-        const double2 kx = *reinterpret_cast<const double2*>(k0 + co + c);
-        const double2 kn = *reinterpret_cast<const double2*>(k1 + co + c);
+      for (int r = 0; r < kRows; ++r) acc[r] = 0.0;
+      double2 x[KP], n[KP], xn[KP], nn[KP];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const double2 qx = *reinterpret_cast<const double2*>(q0 + ro[r] + c);
-          const double2 qn = *reinterpret_cast<const double2*>(q1 + ro[r] + c);
-          acc[r] += fmax(fmax(qx.x * kx.x, qx.x * kn.x), fmax(qn.x * kx.x, qn.x * kn.x));
-          acc[r] += fmax(fmax(qx.y * kx.y, qx.y * kn.y), fmax(qn.y * kx.y, qn.y * kn.y));
+      for (int q = 0; q < KP; ++q) {
+        x[q] = kx[q];
+        n[q] = kn[q];
+      }
+#pragma unroll 1
+      for (int c = 0; c < D / 2; c += KP) {
+        const int cn = min(c + KP, D / 2 - KP);  // the last step re-reads its own
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+          xn[q] = kx[cn + q];
+          nn[q] = kn[cn + q];
+        }
+#pragma unroll
+        for (int q = 0; q < KP; ++q)
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            const double2 a = qs[2 * (r * (D / 2) + c + q)], b = qs[2 * (r * (D / 2) + c + q) + 1];
+            acc[r] += fmax(fmax(a.x * x[q].x, a.x * n[q].x), fmax(b.x * x[q].x, b.x * n[q].x));
+            acc[r] += fmax(fmax(a.y * x[q].y, a.y * n[q].y), fmax(b.y * x[q].y, b.y * n[q].y));
+          }
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+          x[q] = xn[q];
+          n[q] = nn[q];
         }
       }
       if (col < NB) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rr = 4 * r + g4;
-          const double s = acc[r] * p.scale + 0.0;
-          if (rr < kRows) sc[rr * NB + col] = s;
-          if (p.scores && rr < kRows && i0 + rr < NB) p.scores[(bh * NB + i0 + rr) * NB + col] = s;
+        for (int r = 0; r < kRows; ++r) {
+          const double v = acc[r] * p.scale + 0.0;
+          sc[r * NB + col] = v;
+          if (p.scores && i0 + r < NB) p.scores[(bh * NB + i0 + r) * NB + col] = v;
         }
       }
     }
@@ -572,7 +605,8 @@ hipError_t launch_des(const DevGeom& g, const SelectSpec& p, hipStream_t s) {
   // their area with the staged query rows of the score phase
   auto tail = [](int NB) {
     const size_t sel = size_t(kWaves) * 256 * 8 + size_t(NB) * (4 + 1) + kRows;
-    const size_t qst = EST == kEstMean ? size_t(16) * kQsStride<D> * sizeof(double) : 0;
+    const size_t qst = EST == kEstDsa2 ? size_t(kRows) * D * 2 * sizeof(double)
+                                       : size_t(16) * kQsStride<D> * sizeof(double);
     return sel > qst ? sel : qst;
   };
   const size_t lds = size_t(kRows) * g.NB * sizeof(double) + tail(g.NB);
