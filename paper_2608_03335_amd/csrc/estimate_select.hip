@@ -42,19 +42,31 @@ namespace {
 constexpr size_t kLdsPerCu = 160 * 1024;
 template <int D>
 constexpr int kQsStride = D + 2;  // doubles per staged query row
-// A workgroup's item: 12 query rows for 4 waves while the LDS (the score rows, then the
-// histograms or the staged query rows) lets two or more such workgroups share a CU, so
-// that one contracts while another selects. Past that (NB > ~660) a CU holds one
-// workgroup, and one wave per SIMD hides nothing: there it is 16 rows, the whole matrix
-// tile, for 8 waves, which also fetches the key summaries a quarter less often:
-// 528 -> 374 us at 24 heads of 960 blocks (12 rows for 8 waves 445, 12 for 12 409; at 600
-// blocks 189 with the small group, 196 with the large one).
-template <bool WIDE>
+// A workgroup's item of query rows, one of three shapes (rows, waves).
+//  (12, 4): the LDS (the score rows, then the histograms or the staged query rows) lets
+//    two or more such workgroups share a CU: one contracts while another selects.
+//  (16, 8): past that (NB > ~660) a CU holds one workgroup, and one wave per SIMD hides
+//    nothing: here it is 16 rows, the whole matrix tile, for 8 waves, which also fetches
+//    the key summaries a quarter less often: 528 -> 374 us at 24 heads of 960 blocks
+//    (12 rows for 8 waves 445, 12 for 12 409; at 600 blocks 189 with the small group,
+//    196 with the large one).
+//  (4, 4): a launch with at most one item per CU takes as long as one item, and that is
+//    shortest with one row per wave: 35 -> 22 us at 2 heads of 360 blocks, 57 -> 42 at one
+//    of 960; with two items per CU the sixteen-row matrix tile done for four rows is felt
+//    (252 blocks, midpoint intervals, 8 heads: 32 -> 40 us). The exact interval estimator
+//    works per row on the VALU, so there it pays to four items per CU: 70 -> 29 us at 4
+//    heads of 252 blocks, 76 -> 45 at 8, 85 -> 72 at 16.
+template <int ROWS, int WAVES>
 struct Group {
-  static constexpr int rows = WIDE ? 16 : 12;
-  static constexpr int waves = WIDE ? 8 : 4;
+  static constexpr int rows = ROWS;
+  static constexpr int waves = WAVES;
   static constexpr int threads = 64 * waves;
 };
+using FewRows = Group<4, 4>;
+using SharedCu = Group<12, 4>;
+using WholeCu = Group<16, 8>;
+template <int EST>
+constexpr int kFewItems = EST == kEstDsa2 ? 1024 : 256;
 // Register slots per lane of a row's keys (element e = 64 s + lane): SM slots
 // hold rows of up to 64 SM blocks; launches pick the smallest of 4, 8, 16.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -288,14 +300,14 @@ __device__ void intra_topk_marks(const DevGeom& g, const double* sics, int k, in
 
 // Rows of up to 512 blocks (SM <= 8) fit in 128 VGPRs with the DSA2 estimator (up to
 // four waves per SIMD) and in 168 with the others, whose score phase holds two key tiles
-// or two halves of extremes (three waves per SIMD); the LDS (12 score rows + histograms) allows three
-// workgroups per CU either way.
-template <int D, int EST, int SM, bool WIDE>
-__global__ void __launch_bounds__(Group<WIDE>::threads)
+// or two halves of extremes (three waves per SIMD); the LDS (12 score rows + histograms)
+// allows three workgroups per CU either way.
+template <int D, int EST, int SM, class G>
+__global__ void __launch_bounds__(G::threads)
     __attribute__((amdgpu_waves_per_eu(SM <= 8 ? (EST == kEstDsa2 ? 4 : 3) : 1)))
     select_kernel(DevGeom g, SelectSpec p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int kRows = Group<WIDE>::rows, kWaves = Group<WIDE>::waves, kThreads = Group<WIDE>::threads;
+  constexpr int kRows = G::rows, kWaves = G::waves, kThreads = G::threads;
   const int NB = g.NB;
   double* sc = reinterpret_cast<double*>(smem);                           // [kRows][NB]
   uint64_t* hist_w = reinterpret_cast<uint64_t*>(sc + kRows * NB);         // [kWaves][256]
@@ -613,37 +625,42 @@ __global__ void __launch_bounds__(Group<WIDE>::threads)
 
 // LDS of a workgroup: the score rows, then the histograms and marks of the selection
 // phase, which share their area with the staged query rows of the score phase.
-template <int D, int EST, bool WIDE>
+template <int D, int EST, class G>
 constexpr size_t group_lds(int NB) {
-  constexpr int kRows = Group<WIDE>::rows, kWaves = Group<WIDE>::waves;
+  constexpr int kRows = G::rows, kWaves = G::waves;
   const size_t sel = size_t(kWaves) * 256 * 8 + size_t(NB) * (4 + 1) + kRows;
   const size_t qst = EST == kEstDsa2 ? size_t(kRows) * D * 2 * sizeof(double)
                                      : size_t(16) * kQsStride<D> * sizeof(double);
   return size_t(kRows) * NB * sizeof(double) + (sel > qst ? sel : qst);
 }
 
-template <int D, int EST, int SM, bool WIDE>
+template <int D, int EST, int SM, class G>
 hipError_t launch_des(const DevGeom& g, const SelectSpec& p, hipStream_t s) {
-  constexpr int kRows = Group<WIDE>::rows;
-  constexpr size_t lds_max = group_lds<D, EST, WIDE>(kMaxSelectNB);
+  constexpr int kRows = G::rows;
+  constexpr size_t lds_max = group_lds<D, EST, G>(kMaxSelectNB);
   static_assert(lds_max <= kLdsPerCu, "a row group's scores must fit in LDS");
   const hipError_t e = ensure_dynamic_lds(
-      reinterpret_cast<const void*>(&select_kernel<D, EST, SM, WIDE>), int(lds_max));
+      reinterpret_cast<const void*>(&select_kernel<D, EST, SM, G>), int(lds_max));
   if (e != hipSuccess) return e;
   const int64_t items = int64_t(g.B) * g.H * ((g.NB + kRows - 1) / kRows);
   const dim3 grid(unsigned((items + 7) / 8 * 8));  // see the XCD mapping in the kernel
-  select_kernel<D, EST, SM, WIDE>
-      <<<grid, Group<WIDE>::threads, group_lds<D, EST, WIDE>(g.NB), s>>>(g, p);
+  select_kernel<D, EST, SM, G>
+      <<<grid, G::threads, group_lds<D, EST, G>(g.NB), s>>>(g, p);
   return hipGetLastError();
 }
 
 template <int D, int EST>
 hipError_t launch_de(const DevGeom& g, const SelectSpec& p, hipStream_t s) {
-  if (g.NB <= 256) return launch_des<D, EST, 4, false>(g, p, s);
-  if (g.NB <= 512) return launch_des<D, EST, 8, false>(g, p, s);
-  if (2 * group_lds<D, EST, false>(g.NB) <= kLdsPerCu)
-    return launch_des<D, EST, 16, false>(g, p, s);
-  return launch_des<D, EST, 16, true>(g, p, s);
+  if (int64_t(g.B) * g.H * ((g.NB + FewRows::rows - 1) / FewRows::rows) <= kFewItems<EST>) {
+    if (g.NB <= 256) return launch_des<D, EST, 4, FewRows>(g, p, s);
+    if (g.NB <= 512) return launch_des<D, EST, 8, FewRows>(g, p, s);
+    return launch_des<D, EST, 16, FewRows>(g, p, s);
+  }
+  if (g.NB <= 256) return launch_des<D, EST, 4, SharedCu>(g, p, s);
+  if (g.NB <= 512) return launch_des<D, EST, 8, SharedCu>(g, p, s);
+  if (2 * group_lds<D, EST, SharedCu>(g.NB) <= kLdsPerCu)
+    return launch_des<D, EST, 16, SharedCu>(g, p, s);
+  return launch_des<D, EST, 16, WholeCu>(g, p, s);
 }
 
 template <int D>
