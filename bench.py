@@ -168,16 +168,18 @@ def attn_kernel_label(g) -> str:
     return "spade attn_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
 
 
-def traffic_record(kernel_file: str, workload_name: str):
+def traffic_record(kernel_files, workload_name: str):
     """HBM bytes per attention launch from committed rocprofv3 counters, if they
-    were taken on the current kernel source; else None."""
+    were taken on the current kernel sources (one digest over the files); else None."""
     path = os.path.join(ROOT, "profiles", f"attn_{workload_name}_traffic.json")
-    src = os.path.join(ROOT, "paper_2608_03335_amd", "csrc", kernel_file)
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    if rec.get("kernel_sha256") != digest:
+    digest = hashlib.sha256()
+    for f in kernel_files:
+        with open(os.path.join(ROOT, "paper_2608_03335_amd", "csrc", f), "rb") as src:
+            digest.update(src.read())
+    if rec.get("kernel_sha256") != digest.hexdigest():
         return None
     return rec.get("hbm_bytes_per_launch")
 
@@ -459,7 +461,7 @@ def main():
         cpu = cpu_baseline(Q, K, V, cfg, args.cpu_budget, kf)
 
     # the committed counters were taken on the plain Top-P path
-    traffic = traffic_record("attn.hip", args.workload) if args.scheme == "plain" else None
+    traffic = traffic_record(("attn.hip", "attn_walk.h"), args.workload) if args.scheme == "plain" else None
     res = {
         "metric": "sparse-attn ms/call + kept-block bf16 TFLOP/s (% MFMA peak) at ~85% sparsity",
         "value": round(value, 3),
