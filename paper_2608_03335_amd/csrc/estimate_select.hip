@@ -4,10 +4,9 @@
 // scores broadcast and OR-combined with the inter ones, the result united with
 // the window and sink masks), on gfx950.
 //
-// One workgroup (4 waves) owns 12 query-block rows of one head (the MFMA tiles of
-// phase 1 span 16 rows; the 4 past the item are computed and dropped). Small
-// workgroups keep three per CU, so a layer's items fit one round (Hunyuan: 720 items).
-//  1. Scores, the 16 x NB tile parked in LDS, in fp64:
+// One workgroup owns 4, 12 or 16 query-block rows of one head (Group below; the MFMA
+// tiles of phase 1 span 16 rows, those past the item are computed and dropped).
+//  1. Scores, the item's rows parked in LDS, in fp64:
 //     MEAN  S = qbar kbar^T * scale with v_mfma_f64_16x16x4. The contraction
 //           index is permuted so each lane streams 16-byte pieces of the rows.
 //     DSA   per channel max(q~ k_max, q~ k_min) with q~ the query block's
