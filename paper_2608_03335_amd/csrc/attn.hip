@@ -59,6 +59,7 @@ struct Item {
   int64_t bh;
   int i;
   int cnt;  // its kept blocks, clamped to [0, NB]
+  bool stream;  // its keys may be walked as one stream (WalkCursor)
   const int* list_src;
 };
 
@@ -119,6 +120,7 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
     }
     const MultiHead& mh = tab.head[k];
     it.g = tab.geo[mh.geom];
+    it.stream = (tab.streams >> mh.geom) & 1;
     const int local = w - start;  // same residue mod 8 as blockIdx.x
     const int per_xcd = (it.g.NB + 7) / 8;
     const int lo = (local & 7) * per_xcd, r = local >> 3;
@@ -133,6 +135,7 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
     it.list_src = mh.indices + int64_t(b) * mh.indices_bstride + int64_t(it.i) * it.g.NB;
   } else {
     const DevGeom& g = it.g;
+    it.stream = true;  // the launch's own geometry decides
     const int per_xcd = (g.NB + 7) / 8;
     const int64_t slot = int64_t(blockIdx.x) >> 3;
     it.bh = slot / per_xcd;
@@ -219,7 +222,8 @@ __device__ __forceinline__ void row_tile_walk(const Item& it, const uint4* __res
   for (int seg = 0; seg < cnt; seg += LY::SEG) {
     const int ns = min(cnt - seg, LY::SEG);
     if (seg) __syncthreads();
-    const Staged st = stage_list<D, RASTER, STREAM>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT);
+    const Staged st = stage_list<D, RASTER, STREAM>(g, it.list_src + seg, ns, seg ? -2 : j0,
+                                                    it.stream, list, tid, lane, NT);
     const int n = st.chunks;
     if (n == 0) continue;
     WalkCursor<LY::TAB_OFF, W, STREAM> cur(list, ns, st.stream);
@@ -423,7 +427,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
     for (int seg = 0; seg < cnt; seg += LY::SEG) {
       const int ns = min(cnt - seg, LY::SEG);
       if (seg) __syncthreads();
-      const int n = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT).chunks;
+      const int n = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, true,
+                                                  list, tid, lane, NT).chunks;
       if (n == 0) continue;
       // P of "chunk -1" is zero; its V slot must hold finite values
       for (int e = tid; e < LY::TILE / 16; e += 256)
@@ -493,7 +498,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
   for (int seg = 0; seg < cnt; seg += LY::SEG) {
     const int ns = min(cnt - seg, LY::SEG);
     if (seg) __syncthreads();
-    const Staged st = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, list, tid, lane, NT);
+    const Staged st = stage_list<D, RASTER, true>(g, it.list_src + seg, ns, seg ? -2 : j0, true,
+                                                  list, tid, lane, NT);
     const int n = st.chunks;
     if (n == 0) continue;
     __builtin_amdgcn_s_waitcnt(0);  // Q and list loads are done: only DMA is counted below
@@ -1026,11 +1032,10 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
   };
   // the walk over concatenated keys where it saves chunks (WalkCursor)
   bool stream = false;
-  if constexpr (MULTI) {
-    for (int k = 0; k < tab->n_heads; ++k) stream |= saves_chunks(tab->geo[tab->head[k].geom]);
-  } else {
+  if constexpr (MULTI)
+    stream = tab->streams != 0;
+  else
     stream = saves_chunks(g);
-  }
 #define SPADE_ATTN_WALK(w)                                                             \
   (stream ? walk(attn_kernel<D, w, RASTER, MULTI, true>, WalkLayout<D, w>{}, w)        \
           : walk(attn_kernel<D, w, RASTER, MULTI, false>, WalkLayout<D, w>{}, w))
@@ -1218,6 +1223,10 @@ hipError_t launch_sparse_attn_multi(const DevGeom* geo, int n_geo, const MultiHe
       mh.start = start;
       start += (gh.NB + 7) / 8 * 8;
       tab.head[tab.n_heads++] = mh;
+      // Each geometry decides for itself whether its keys are a stream: a head's chunks, and
+      // with them the rounding of its output, must not depend on the launch's other heads.
+      // Heads that are not streamed run chunk by chunk in a streaming instance as well.
+      if (saves_chunks(gh)) tab.streams |= 1u << mh.geom;
       if (widest < 0 || gh.BS > geo[widest].BS) widest = heads[hh].geom;
     }
     if (tab.n_heads == 0) continue;

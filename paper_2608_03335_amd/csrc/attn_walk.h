@@ -194,11 +194,12 @@ struct Staged {
 // chunk, and every block has at least kChunk keys (so a chunk spans at most two of them),
 // the walk runs over the concatenated keys and only the last chunk is partly empty: 10%
 // fewer chunks for blocks of 144 keys, 6% for 120 (12 heads of 32760 tokens, every block
-// kept: 8.40 -> 7.60 ms). j0: the entry of index tid, loaded earlier (-2: not loaded). Every
-// wave returns the same result.
+// kept: 8.40 -> 7.60 ms); `may` = false (uniform) keeps it from that. j0: the entry of index
+// tid, loaded earlier (-2: not loaded). Every wave returns the same result.
 template <int D, bool RASTER, bool STREAM>
 __device__ __forceinline__ Staged stage_list(const DevGeom& g, const int* src, int ns,
-                                             int j0, lds_int* list, int tid, int lane, int nt) {
+                                             int j0, bool may, lds_int* list, int tid, int lane,
+                                             int nt) {
   for (int e = tid; e < ns; e += nt) {
     const int j = e == tid && j0 != -2 ? j0 : src[e];
     int2 ent = make_int2(0, 0);
@@ -223,7 +224,7 @@ __device__ __forceinline__ Staged stage_list(const DevGeom& g, const int* src, i
   }
   keys = wave_sum(keys);
   apart = wave_sum(apart);
-  const bool stream = STREAM && __ballot(small) == 0 && __ballot(part) != 0;
+  const bool stream = STREAM && may && __ballot(small) == 0 && __ballot(part) != 0;
   return {stream ? (keys + kChunk - 1) / kChunk : apart, stream};
 }
 

@@ -168,6 +168,7 @@ struct MultiTable {
   MultiHead head[kMaxMultiHeads];
   int n_heads;              // heads of this launch, in ascending `start`
   int items_per_batch;      // work items per batch element (a multiple of 8)
+  uint32_t streams;         // bit c: keys under geo[c] may be walked as one stream
 };
 // One launch per distinct workgroup shape (compute waves = ceil(BS / 32)); heads
 // whose blockings share a shape run in the same launch.
