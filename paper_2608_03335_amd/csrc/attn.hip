@@ -600,7 +600,7 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
       float *__restrict__ lse, const int *__restrict__ order,                                 \
       typename std::conditional<MULTI, MultiTable, NoTable>::type tab
 constexpr int kSwBlocks = 3824, kPpBlocks = 7928;
-constexpr int kLoaderItems = 8192;
+constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;
 
 template <int D, int W, bool RASTER, bool MULTI, bool STREAM>
 __global__ void __launch_bounds__(W == 5 ? 512 : 64 * W)
@@ -982,6 +982,17 @@ bool saves_chunks(const DevGeom& g) {
   return 100 * (chunks * kChunk - keys) >= 3 * chunks * kChunk;
 }
 
+// Whether a geometry's rows may be walked as a stream at all: decided by the geometry alone,
+// so that a head's rounding does not depend on what else its call holds. Blocks of 64 slots
+// at d = 128 are not: their large launches run the loader kernel, which cuts each block into
+// chunks of its own, and a walk that does the same gives the same bits. With the 6% that a
+// ragged axis leaves to save, the stream was no faster there (960 blocks, 24 heads: 9.83 ms
+// apart, 9.89 as a stream; 252 blocks, 12 heads: 0.380, 0.384).
+bool may_stream(const DevGeom& g) {
+  if (g.d == 128 && g.BS == 64) return false;
+  return saves_chunks(g);
+}
+
 // Launches `kernel` (one of the above, all with the same arguments) over the work items.
 template <bool MULTI, class Kernel>
 hipError_t launch_items(Kernel kernel, int threads, size_t lds, int max_lds, const DevGeom& g,
@@ -1035,19 +1046,22 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
   if constexpr (MULTI)
     stream = tab->streams != 0;
   else
-    stream = saves_chunks(g);
+    stream = may_stream(g);
 #define SPADE_ATTN_WALK(w)                                                             \
   (stream ? walk(attn_kernel<D, w, RASTER, MULTI, true>, WalkLayout<D, w>{}, w)        \
           : walk(attn_kernel<D, w, RASTER, MULTI, false>, WalkLayout<D, w>{}, w))
   switch ((g.BS + 31) / 32) {
     case 1: return SPADE_ATTN_WALK(1);
     case 2:
-      // 64-token blocks at d = 128 load 16 KB per 64 query rows and chunk. Launches of many
-      // rounds are bound by those loads, which a wave of its own keeps further ahead (4.84
-      // against 5.06 ms at 11520 items); shorter ones by a work item's latency (0.45 against
-      // 0.58 ms at 2016 items).
+      // Blocks of 33..64 slots at d = 128 load 16 KB per 64 query rows and chunk. In large
+      // launches over long rows a loading wave of its own keeps those loads further ahead;
+      // it walks block by block, so it takes rows that are not a stream, and gives the bits of
+      // the walk. Loader against walk (64 slots, Top-P lists, range over two inputs):
+      // +3..+6% at 768 to 960 blocks from 4608 items on, +1..+4% at 616 and 720 blocks;
+      // -2..-7% at 600 blocks, -7..-17% at 252 to 504; -3% at 960 blocks and 2880 items.
       if constexpr (D == 128) {
-        if (items >= kLoaderItems) return loader(attn_loader_kernel<D, 2, RASTER, MULTI>, 2);
+        if (!stream && items >= kLoaderItems && nb_max >= kLoaderBlocks)
+          return loader(attn_loader_kernel<D, 2, RASTER, MULTI>, 2);
       }
       return SPADE_ATTN_WALK(2);
     case 3: return SPADE_ATTN_WALK(3);
@@ -1226,7 +1240,7 @@ hipError_t launch_sparse_attn_multi(const DevGeom* geo, int n_geo, const MultiHe
       // Each geometry decides for itself whether its keys are a stream: a head's chunks, and
       // with them the rounding of its output, must not depend on the launch's other heads.
       // Heads that are not streamed run chunk by chunk in a streaming instance as well.
-      if (saves_chunks(gh)) tab.streams |= 1u << mh.geom;
+      if (may_stream(gh)) tab.streams |= 1u << mh.geom;
       if (widest < 0 || gh.BS > geo[widest].BS) widest = heads[hh].geom;
     }
     if (tab.n_heads == 0) continue;

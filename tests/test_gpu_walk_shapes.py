@@ -5,7 +5,7 @@ that saves enough chunks, as one stream in which a chunk can span blocks; lists 
 in segments (256 entries for blocks of up to 64 slots, 512 for 129..160, 1024 for the
 others); launches of more than 256 work items are ranked, by one workgroup up to 1024
 (batch, head) pairs; 64-slot blocks at d = 128 take the kernel with a loading wave from
-8192 work items on. Each case sits on one of these edges. The tolerances are those of
+4096 work items and 608 blocks on. Each case sits on one of these edges. The tolerances are those of
 every attention parity test (bf16 inputs and weights, fp32 accumulation).
 """
 import numpy as np
@@ -118,8 +118,11 @@ def test_ranking_launches(d, H, n):
     _check((n, 4, 8), (1, 4, 8), d, H, LENGTHS, True, heads=[0, 1, H - 1])
 
 
-@pytest.mark.parametrize("H", [21, 22])
-def test_loading_wave_threshold(H):
-    print("loading wave", H, flush=True)  # 384 blocks per head
-    _check((8, 45, 60), (1, 8, 8), 128, H, (3, 9, 30, 12, 0), True, rows=range(0, 384, 23),
+@pytest.mark.parametrize("raster", [True, False], ids=["raster", "blocked"])
+@pytest.mark.parametrize("H,grid", [(6, (19, 32, 64)), (7, (19, 32, 64)), (7, (15, 40, 64)),
+                                    (7, (16, 37, 64))])
+def test_loading_wave_threshold(H, grid, raster):
+    # 608, 608, 600 and 640 blocks per head; the last grid is ragged along y
+    print("loading wave", H, grid, raster, flush=True)
+    _check(grid, (1, 8, 8), 128, H, (3, 9, 30, 12, 0), raster, rows=range(0, 600, 37),
            heads=[0, H - 1])
