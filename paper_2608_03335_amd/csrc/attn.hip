@@ -600,7 +600,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
       float *__restrict__ lse, const int *__restrict__ order,                                 \
       typename std::conditional<MULTI, MultiTable, NoTable>::type tab
 constexpr int kSwBlocks = 3824, kPpBlocks = 7928;
-constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;
+constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;  // at d = 128
+constexpr int kLoaderItems64 = 640;                      // at d = 64
 
 template <int D, int W, bool RASTER, bool MULTI, bool STREAM>
 __global__ void __launch_bounds__(W == 5 ? 512 : 64 * W)
@@ -747,8 +748,9 @@ __device__ __forceinline__ void loader_chunk(const DevGeom& g, const char* kb, c
 
 // Single-buffered phases with a loader wave: W compute waves (32 query slots each) and one
 // more that issues all loads of the next chunk while this one is computed (two LDS
-// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the two shapes
-// where it beats the pipelined walk (see the dispatch).
+// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the three shapes
+// where it beats the pipelined walk (see the dispatch). The same arithmetic in the same order
+// as a walk that is not a stream: either gives the same bits.
 template <int D, int W, bool RASTER, bool MULTI>
 __global__ void __launch_bounds__(64 * (W + 1))
     __attribute__((amdgpu_waves_per_eu(3)))
@@ -987,9 +989,10 @@ bool saves_chunks(const DevGeom& g) {
 // at d = 128 are not: their large launches run the loader kernel, which cuts each block into
 // chunks of its own, and a walk that does the same gives the same bits. With the 6% that a
 // ragged axis leaves to save, the stream was no faster there (960 blocks, 24 heads: 9.83 ms
-// apart, 9.89 as a stream; 252 blocks, 12 heads: 0.380, 0.384).
+// apart, 9.89 as a stream; 252 blocks, 12 heads: 0.380, 0.384). Nor are those of 161..224
+// slots at d = 64, whose large launches run that kernel too.
 bool may_stream(const DevGeom& g) {
-  if (g.d == 128 && g.BS == 64) return false;
+  if (g.d == 128 ? g.BS == 64 : g.BS > 160 && g.BS <= 224) return false;
   return saves_chunks(g);
 }
 
@@ -1047,9 +1050,10 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
     stream = tab->streams != 0;
   else
     stream = may_stream(g);
+#define SPADE_ATTN_APART(w) walk(attn_kernel<D, w, RASTER, MULTI, false>, WalkLayout<D, w>{}, w)
 #define SPADE_ATTN_WALK(w)                                                             \
   (stream ? walk(attn_kernel<D, w, RASTER, MULTI, true>, WalkLayout<D, w>{}, w)        \
-          : walk(attn_kernel<D, w, RASTER, MULTI, false>, WalkLayout<D, w>{}, w))
+          : SPADE_ATTN_APART(w))
   switch ((g.BS + 31) / 32) {
     case 1: return SPADE_ATTN_WALK(1);
     case 2:
@@ -1074,7 +1078,17 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
         if (nb_max <= kPpBlocks) return five(attn_pp_kernel<D, 5, RASTER, MULTI>);
         return five(attn_kernel<D, 5, RASTER, MULTI, true>);
       }
-    case 6: return SPADE_ATTN_WALK(6);
+    case 6:
+      // At d = 64 four of the loader kernel's waves (101 registers) fit a SIMD, three of the
+      // walk's (157). Launches of more than 2.5 items per CU, loader against walk: 1.56, 1.85 ms
+      // (224 blocks of 192 slots, 12 heads), 1.09, 1.27 (320, 4 heads); shorter ones are bound
+      // by an item's latency: 0.147, 0.126 ms (50, 4 heads).
+      if constexpr (D == 64) {
+        if (items > kLoaderItems64) return loader(attn_loader_kernel<D, 6, RASTER, MULTI>, 6);
+        return SPADE_ATTN_APART(6);
+      } else {
+        return SPADE_ATTN_WALK(6);
+      }
     case 7:
       // at d = 64 seven waves of up to 128 registers plus a loader leave room for two
       // workgroups per CU, the walk's seven of 157 for one: 3.23 against 3.47 ms (57600
@@ -1086,6 +1100,7 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
     case 8: return SPADE_ATTN_WALK(8);
   }
 #undef SPADE_ATTN_WALK
+#undef SPADE_ATTN_APART
   return hipErrorInvalidValue;
 }
 

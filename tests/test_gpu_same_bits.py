@@ -44,7 +44,7 @@ def _same(a, b):
 # (its edge blocks along y waste 2% of the chunks); both have the same number of row tiles.
 @pytest.mark.parametrize("d,grid,blocks", [
     (128, (4, 45, 32), ((2, 8, 8), (3, 5, 8))), (64, (4, 45, 32), ((2, 8, 8), (3, 5, 8))),
-    (128, (6, 47, 72), ((3, 4, 8), (2, 5, 9))), (64, (6, 51, 48), ((3, 8, 8), (3, 7, 8)))],
+    (128, (6, 47, 72), ((3, 4, 8), (2, 5, 9))), (64, (35, 24, 24), ((16, 4, 4), (5, 6, 8)))],
     ids=str)
 @pytest.mark.parametrize("swap", [False, True])
 def test_multi_equals_own_blocking(d, grid, blocks, swap):
@@ -90,7 +90,8 @@ def _short_lists(H, NB, longest, seed):
 # ragged axis (the edge blocks' keys do not fill their chunks) and, last, none.
 @pytest.mark.parametrize("d,grid,block,H", [
     (128, (16, 37, 64), (1, 8, 8), 13), (128, (16, 37, 64), (1, 8, 8), 6),
-    (128, (16, 32, 80), (1, 8, 8), 13)], ids=str)
+    (128, (16, 32, 80), (1, 8, 8), 13), (64, (8, 26, 40), (4, 6, 8), 13),
+    (64, (6, 33, 40), (3, 7, 8), 13)], ids=str)
 def test_many_heads_equal_one(d, grid, block, H):
     print("many heads against one", d, grid, block, H, flush=True)
     g, g1 = S.geom(1, H, d, *grid, *block), S.geom(1, 1, d, *grid, *block)

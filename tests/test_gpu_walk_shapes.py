@@ -4,9 +4,10 @@ A row's kept keys are walked in chunks of 32, either chunk by chunk of each bloc
 that saves enough chunks, as one stream in which a chunk can span blocks; lists are staged
 in segments (256 entries for blocks of up to 64 slots, 512 for 129..160, 1024 for the
 others); launches of more than 256 work items are ranked, by one workgroup up to 1024
-(batch, head) pairs; 64-slot blocks at d = 128 take the kernel with a loading wave from
-4096 work items and 608 blocks on. Each case sits on one of these edges. The tolerances are those of
-every attention parity test (bf16 inputs and weights, fp32 accumulation).
+(batch, head) pairs; the kernel with a loading wave takes 64-slot blocks at d = 128
+from 4096 work items and 608 blocks on and 161..192-slot ones at d = 64 past 640 items.
+Each case sits on one of these edges. The tolerances are those of every attention parity
+test (bf16 inputs and weights, fp32 accumulation).
 """
 import numpy as np
 import pytest
@@ -118,11 +119,16 @@ def test_ranking_launches(d, H, n):
     _check((n, 4, 8), (1, 4, 8), d, H, LENGTHS, True, heads=[0, 1, H - 1])
 
 
+# 608, 608, 600 and 640 blocks per head (64 slots; the last grid is ragged along y); 50 of
+# 192 and of 168 slots
 @pytest.mark.parametrize("raster", [True, False], ids=["raster", "blocked"])
-@pytest.mark.parametrize("H,grid", [(6, (19, 32, 64)), (7, (19, 32, 64)), (7, (15, 40, 64)),
-                                    (7, (16, 37, 64))])
-def test_loading_wave_threshold(H, grid, raster):
-    # 608, 608, 600 and 640 blocks per head; the last grid is ragged along y
-    print("loading wave", H, grid, raster, flush=True)
-    _check(grid, (1, 8, 8), 128, H, (3, 9, 30, 12, 0), raster, rows=range(0, 600, 37),
+@pytest.mark.parametrize("d,H,grid,block", [
+    (128, 6, (19, 32, 64), (1, 8, 8)), (128, 7, (19, 32, 64), (1, 8, 8)),
+    (128, 7, (15, 40, 64), (1, 8, 8)), (128, 7, (16, 37, 64), (1, 8, 8)),
+    (64, 12, (8, 26, 40), (4, 6, 8)), (64, 13, (8, 26, 40), (4, 6, 8)),
+    (64, 13, (6, 33, 40), (3, 7, 8))], ids=str)
+def test_loading_wave_threshold(d, H, grid, block, raster):
+    print("loading wave", d, H, grid, block, raster, flush=True)
+    NB = S.geom(1, H, d, *grid, *block).NB
+    _check(grid, block, d, H, (3, 9, 30, 12, 0), raster, rows=range(0, NB, max(7, NB // 16)),
            heads=[0, H - 1])
