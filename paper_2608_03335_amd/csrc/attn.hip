@@ -748,7 +748,7 @@ __device__ __forceinline__ void loader_chunk(const DevGeom& g, const char* kb, c
 
 // Single-buffered phases with a loader wave: W compute waves (32 query slots each) and one
 // more that issues all loads of the next chunk while this one is computed (two LDS
-// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the three shapes
+// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the four shapes
 // where it beats the pipelined walk (see the dispatch). The same arithmetic in the same order
 // as a walk that is not a stream: either gives the same bits.
 template <int D, int W, bool RASTER, bool MULTI>
@@ -985,14 +985,15 @@ bool saves_chunks(const DevGeom& g) {
 }
 
 // Whether a geometry's rows may be walked as a stream at all: decided by the geometry alone,
-// so that a head's rounding does not depend on what else its call holds. Blocks of 64 slots
-// at d = 128 are not: their large launches run the loader kernel, which cuts each block into
-// chunks of its own, and a walk that does the same gives the same bits. With the 6% that a
-// ragged axis leaves to save, the stream was no faster there (960 blocks, 24 heads: 9.83 ms
-// apart, 9.89 as a stream; 252 blocks, 12 heads: 0.380, 0.384). Nor are those of 161..224
-// slots at d = 64, whose large launches run that kernel too.
+// so that a head's rounding does not depend on what else its call holds. Blocks of 64 and 96
+// slots at d = 128 are not: their large launches run the loader kernel, which cuts each block
+// into chunks of its own, and a walk that does the same gives the same bits. With the 6% that
+// a ragged axis leaves to save, the stream was no faster there (960 blocks of 64 slots, 24
+// heads: 9.83 ms apart, 9.89 as a stream; 252, 12 heads: 0.380, 0.384; 392 of 96 slots, 8
+// heads: 0.902, 0.915). Nor are those of 161..224 slots at d = 64, whose large launches run
+// that kernel too.
 bool may_stream(const DevGeom& g) {
-  if (g.d == 128 ? g.BS == 64 : g.BS > 160 && g.BS <= 224) return false;
+  if (g.d == 128 ? g.BS == 64 || g.BS == 96 : g.BS > 160 && g.BS <= 224) return false;
   return saves_chunks(g);
 }
 
@@ -1068,7 +1069,15 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
           return loader(attn_loader_kernel<D, 2, RASTER, MULTI>, 2);
       }
       return SPADE_ATTN_WALK(2);
-    case 3: return SPADE_ATTN_WALK(3);
+    case 3:
+      // Large launches of rows that are not a stream (same bits either way): with the walk
+      // 96-slot blocks took 0..2% longer than with the loading wave (24 heads of 392 blocks,
+      // blocked: 3.016 against 2.956 ms; of 720: 7.12, 6.98); at 2016 items and fewer the walk
+      // is 1..29% faster.
+      if constexpr (D == 128) {
+        if (!stream && items >= kLoaderItems) return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);
+      }
+      return SPADE_ATTN_WALK(3);
     case 4: return SPADE_ATTN_WALK(4);
     case 5:
       if constexpr (D == 64) {
