@@ -4,10 +4,10 @@ A row's kept keys are walked in chunks of 32, either chunk by chunk of each bloc
 that saves enough chunks, as one stream in which a chunk can span blocks; lists are staged
 in segments (256 entries for blocks of up to 64 slots, 512 for 129..160, 1024 for the
 others); launches of more than 256 work items are ranked, by one workgroup up to 1024
-(batch, head) pairs; the kernel with a loading wave takes 64-slot blocks at d = 128
-from 4096 work items and 608 blocks on, 65..96-slot ones there from 4096 items on and
-161..192-slot ones at d = 64 past 640 items. Each case sits on one of these edges. The
-tolerances are those of every attention parity test (bf16 inputs and weights, fp32
+(batch, head) pairs and 24576 counts; the kernel with a loading wave takes 64-slot blocks
+at d = 128 from 4096 work items and 608 blocks on, 65..96-slot ones there from 4096 items
+on and 161..192-slot ones at d = 64 past 640 items. Each case sits on one of these edges.
+The tolerances are those of every attention parity test (bf16 inputs and weights, fp32
 accumulation).
 """
 import numpy as np
@@ -114,7 +114,8 @@ def test_list_segments(d, block, n, lengths):
            rows=range(len(lengths)))
 
 
-@pytest.mark.parametrize("d,H,n", [(64, 4, 64), (128, 3, 86), (64, 1025, 2)])
+@pytest.mark.parametrize("d,H,n", [(64, 4, 64), (128, 3, 86), (64, 192, 128), (64, 193, 128),
+                                   (64, 1025, 2)])
 def test_ranking_launches(d, H, n):
     print("ranking", d, H, n, flush=True)
     _check((n, 4, 8), (1, 4, 8), d, H, LENGTHS, True, heads=[0, 1, H - 1])
