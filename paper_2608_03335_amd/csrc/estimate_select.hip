@@ -44,11 +44,13 @@ constexpr int kQsStride = D + 2;  // doubles per staged query row
 // A workgroup's item of query rows, one of three shapes (rows, waves).
 //  (12, 4): the LDS (the score rows, then the histograms or the staged query rows) lets
 //    two or more such workgroups share a CU: one contracts while another selects.
-//  (16, 8): past that (NB > ~660) a CU holds one workgroup, and one wave per SIMD hides
-//    nothing: here it is 16 rows, the whole matrix tile, for 8 waves, which also fetches
-//    the key summaries a quarter less often: 528 -> 374 us at 24 heads of 960 blocks
-//    (12 rows for 8 waves 445, 12 for 12 409; at 600 blocks 189 with the small group,
-//    196 with the large one).
+//  (16, 8): past that a CU holds one workgroup (NB > 729 at d = 64 and 680 at d = 128, for
+//    the exact interval estimator 725 and 597), and one wave per SIMD hides nothing: here it
+//    is 16 rows, the whole matrix tile, for 8 waves, which also fetches the key summaries a
+//    quarter less often: 528 -> 374 us at 24 heads of 960 blocks (12 rows for 8 waves 445, 12
+//    for 12 409; at 600 blocks 189 with the small group, 196 with the large one). A launch
+//    that fitted one round of two small workgroups per CU pays for it: 128 -> 148 us at 8
+//    heads of 700 blocks, midpoint intervals.
 //  (4, 4): a launch with at most one item per CU takes as long as one item, and that is
 //    shortest with one row per wave: 35 -> 22 us at 2 heads of 360 blocks, 57 -> 42 at one
 //    of 960; with two items per CU the sixteen-row matrix tile done for four rows is felt
@@ -297,10 +299,11 @@ __device__ void intra_topk_marks(const DevGeom& g, const double* sics, int k, in
   }
 }
 
-// Rows of up to 512 blocks (SM <= 8) fit in 128 VGPRs with the DSA2 estimator (up to
-// four waves per SIMD) and in 168 with the others, whose score phase holds two key tiles
-// or two halves of extremes (three waves per SIMD); the LDS (12 score rows + histograms)
-// allows three workgroups per CU either way.
+// Registers of rows of up to 512 blocks (SM <= 8): at most 115 with the DSA2 estimator (four
+// waves per SIMD). The others' score phase holds two key tiles or two halves of extremes: at
+// d = 128 it takes the 168 that three waves per SIMD leave, and the mean estimator's 12-row
+// form spills 4 beyond them (20 bytes a lane). The LDS (12 score rows + histograms) allows
+// three workgroups per CU either way.
 template <int D, int EST, int SM, class G>
 __global__ void __launch_bounds__(G::threads)
     __attribute__((amdgpu_waves_per_eu(SM <= 8 ? (EST == kEstDsa2 ? 4 : 3) : 1)))
@@ -390,7 +393,8 @@ __global__ void __launch_bounds__(G::threads)
       // DSA: A = q~ = (qmax + qmin)/2 (staged as above) against B = k_c, then |q~| against
       // k_r. Half a key tile's extremes (64 registers) are in flight while the other half is
       // contracted; loading each tile when it was needed left the contraction waiting:
-      // 122 -> 104 us at 24 heads of 360 blocks.
+      // 122 -> 104 us at 24 heads of 360 blocks (where a CU has one or two workgroups in all it
+      // costs 3 to 6%: 71.6 -> 74.8 at 12 heads).
       constexpr int HQ = KQ / 2;
       double* qs = reinterpret_cast<double*>(hist_w);  // [16][kQsStride]
       for (int e = threadIdx.x; e < 16 * D; e += kThreads) {

@@ -5,7 +5,8 @@ The summaries are small whole numbers, even where an estimator halves them, so e
 score is exact in fp64 whatever the order of its sum and ties are plentiful: kept sets
 and counts must equal the oracle's, with no exemption. Sizes are (heads, blocks): the
 4-row group takes launches of up to 256 items (1024 for the exact interval estimator,
-`dsa2`), the 16-row group starts where two 12-row workgroups no longer fit in 160 KB.
+`dsa2`), the 16-row group starts where two 12-row workgroups no longer fit in 160 KB:
+above 729 blocks at d = 64 and 680 at d = 128 (725 and 597 for `dsa2`).
 """
 import numpy as np
 import pytest
@@ -23,11 +24,14 @@ DEV = "cuda"
 
 @pytest.mark.parametrize("est,d,H,NB", [
     ("mean", 128, 2, 9), ("mean", 64, 4, 256), ("mean", 128, 4, 257), ("mean", 128, 1, 1024),
-    ("mean", 64, 2, 641), ("mean", 128, 3, 653), ("mean", 128, 3, 673), ("mean", 64, 2, 1024),
-    ("dsa", 64, 3, 65), ("dsa", 128, 4, 253), ("dsa", 128, 5, 253), ("dsa", 128, 2, 1021),
-    ("dsa", 64, 2, 530),
+    ("mean", 64, 2, 641), ("mean", 128, 3, 680), ("mean", 128, 3, 681), ("mean", 128, 2, 1024),
+    ("mean", 64, 2, 729), ("mean", 64, 2, 730), ("mean", 64, 2, 1024),
+    ("dsa", 64, 3, 65), ("dsa", 128, 4, 253), ("dsa", 128, 5, 253), ("dsa", 128, 2, 680),
+    ("dsa", 128, 2, 681), ("dsa", 128, 2, 1021), ("dsa", 64, 2, 530), ("dsa", 64, 2, 729),
+    ("dsa", 64, 2, 730),
     ("dsa2", 64, 1, 1), ("dsa2", 128, 4, 65), ("dsa2", 128, 5, 1024), ("dsa2", 64, 4, 1021),
-    ("dsa2", 128, 17, 251), ("dsa2", 128, 9, 513)])
+    ("dsa2", 64, 5, 1021), ("dsa2", 128, 17, 251), ("dsa2", 128, 9, 513), ("dsa2", 128, 7, 597),
+    ("dsa2", 128, 7, 598), ("dsa2", 64, 6, 725), ("dsa2", 64, 6, 726)])
 def test_row_groups_exact(est, d, H, NB):
     cfg = P.small_cfg(1, 1, NB, 1, 1, 1, d=d, H=H)
     print("row groups", est, d, H, NB, flush=True)
