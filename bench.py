@@ -158,13 +158,19 @@ def cpu_baseline(Q, K, V, cfg, budget_s: float, call_flops: float) -> dict:
 
 def attn_kernel_label(g) -> str:
     """Which attention kernel the library launches for this blocking: blocks of 5 row tiles
-    (129..160 slots) run the 8-wave walk as attn_sw_kernel (d = 128, at most 3824 blocks)
-    or attn_pp_kernel (d = 64, or at most 7928 blocks), everything else attn_kernel."""
-    tiles = -(-g.bt * g.bh * g.bw // 32)
-    if tiles == 5 and g.d == 128 and g.NB <= 3824:
+    (129..160 slots) run the 8-wave walk, attn_sw_kernel; large launches of 64- and 96-slot
+    blocks at d = 128 and of 161..192-slot ones at d = 64, and every launch of 193..224-slot
+    ones there, the kernel with a loading wave; everything else attn_kernel."""
+    slots, items = g.bt * g.bh * g.bw, g.B * g.H * g.NB
+    tiles = -(-slots // 32)
+    if tiles == 5:
         return "spade attn_sw_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
-    if tiles == 5 and (g.d == 64 or g.NB <= 7928):
-        return "spade attn_pp_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
+    if g.d == 128:
+        loader = items >= 4096 and (slots == 96 or (slots == 64 and g.NB >= 608))
+    else:
+        loader = tiles == 7 or (tiles == 6 and items > 640)
+    if loader:
+        return "spade attn_loader_kernel (loading wave, bf16 MFMA 32x32x16)"
     return "spade attn_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
 
 

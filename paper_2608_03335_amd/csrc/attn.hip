@@ -153,9 +153,10 @@ __device__ __forceinline__ Item work_item(const DevGeom& g_arg, const int* count
 }
 
 // Workgroups of W waves, wave w on query slots 32 w .. 32 w + 31 for the whole walk, two
-// waves per SIMD (three at d = 64, where a step needs at most 166 registers): 8 / W
-// workgroups share a CU, so barriers of one are filled by another. The waves issue the DMA
-// themselves, 1 / W of a chunk's loads each, from inside their steps.
+// waves per SIMD (three at d = 64: 152..168 registers, and 2 spilled where three waves walk
+// raster rows as a stream): 8 / W workgroups share a CU, so barriers of one are filled by
+// another. The waves issue the DMA themselves, 1 / W of a chunk's loads each, from inside
+// their steps.
 // Rings of two K and two V tiles: in step c, after the sync in slot SY, K(c + 1) and
 // V(c - 1) have been read by every wave (their reads are in slots <= NS / 2 - 1), so K(c +
 // 3) and V(c + 1) are issued into their place; they are waited for at the next sync, a
@@ -349,7 +350,7 @@ __device__ __forceinline__ void row_tile_walk(const Item& it, const uint4* __res
 // Against waves that read K of c + 1 and V^T of c in their own step, with whole swizzled
 // rows and a 9-chunk ring: 57600-token, 24-head layer of 160-slot blocks 6.40 -> 5.59 ms,
 // 32760-token, 12-head layer of 144-slot blocks 1.22 -> 1.00 ms, d = 64 against the
-// paired kernel 2.23 -> 1.79 ms (two batches of 16 heads, 19890 tokens).
+// paired kernel before it 2.23 -> 1.79 ms (two batches of 16 heads, 19890 tokens).
 template <int D>
 struct FiveTileLayout {
   static constexpr int TILE = KvTile<D>::BYTES, T = 5;
@@ -589,43 +590,28 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
 }
 
 // Kernels. MULTI (raster only): one launch over heads with different blockings; the work
-// item picks its head, and with it the geometry and block lists, from `tab`. Blocks of 5
-// row tiles run the same walk under three names, which traces and the bench's label tell
-// apart: attn_sw_kernel (d = 128, lists of at most kSwBlocks blocks), attn_pp_kernel (d =
-// 64, or lists of at most kPpBlocks), attn_kernel (longer ones).
+// item picks its head, and with it the geometry and block lists, from `tab`.
 #define SPADE_ATTN_ARGS                                                                       \
   DevGeom g_arg, const uint4 *__restrict__ qb, const char *__restrict__ kb,                   \
       const char *__restrict__ vb, const int *__restrict__ counts,                            \
       const int *__restrict__ indices, float scale_log2, __bf16 *__restrict__ ob,             \
       float *__restrict__ lse, const int *__restrict__ order,                                 \
       typename std::conditional<MULTI, MultiTable, NoTable>::type tab
-constexpr int kSwBlocks = 3824, kPpBlocks = 7928;
 constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;  // at d = 128
 constexpr int kLoaderItems64 = 640;                      // at d = 64
 
 template <int D, int W, bool RASTER, bool MULTI, bool STREAM>
-__global__ void __launch_bounds__(W == 5 ? 512 : 64 * W)
-    __attribute__((amdgpu_waves_per_eu(D == 64 && W != 5 ? 3 : 2))) attn_kernel(SPADE_ATTN_ARGS) {
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+    attn_kernel(SPADE_ATTN_ARGS) {
   extern __shared__ __align__(16) char smem_raw[];
   const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
-  if (it.i < 0) return;
-  if constexpr (W == 5)
-    five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
-  else
+  if (it.i >= 0)
     row_tile_walk<D, W, RASTER, STREAM>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
 }
 
-template <int D, int W, bool RASTER, bool MULTI>
+template <int D, bool RASTER, bool MULTI>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
     attn_sw_kernel(SPADE_ATTN_ARGS) {
-  extern __shared__ __align__(16) char smem_raw[];
-  const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
-  if (it.i >= 0) five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
-}
-
-template <int D, int W, bool RASTER, bool MULTI>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
-    attn_pp_kernel(SPADE_ATTN_ARGS) {
   extern __shared__ __align__(16) char smem_raw[];
   const Item it = work_item<MULTI>(g_arg, counts, indices, order, tab);
   if (it.i >= 0) five_tile_walk<D, RASTER, MULTI>(it, qb, kb, vb, scale_log2, ob, lse, smem_raw);
@@ -1036,9 +1022,6 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
     return launch_items<MULTI>(kernel, threads, lds, max_lds, g, qb, kb, vb, counts, indices,
                                scale_log2, ob, lse, s, tab, order);
   };
-  auto five = [&](auto kernel) {
-    return run(kernel, 512, FiveTileLayout<D>::BYTES, FiveTileLayout<D>::BYTES);
-  };
   auto loader = [&](auto kernel, int w) {
     return run(kernel, 64 * (w + 1), size_t(nb_max) * sizeof(int), int(kMaxAttnNB * sizeof(int)));
   };
@@ -1056,16 +1039,16 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
   (stream ? walk(attn_kernel<D, w, RASTER, MULTI, true>, WalkLayout<D, w>{}, w)        \
           : SPADE_ATTN_APART(w))
   switch ((g.BS + 31) / 32) {
-    case 1: return SPADE_ATTN_WALK(1);
+    case 1: return SPADE_ATTN_APART(1);  // a stream needs blocks of more than a chunk
     case 2:
-      // Blocks of 33..64 slots at d = 128 load 16 KB per 64 query rows and chunk. In large
+      // Blocks of 64 slots at d = 128 load 16 KB per 64 query rows and chunk. In large
       // launches over long rows a loading wave of its own keeps those loads further ahead;
       // it walks block by block, so it takes rows that are not a stream, and gives the bits of
-      // the walk. Loader against walk (64 slots, Top-P lists, range over two inputs):
+      // the walk. Loader against walk (Top-P lists, range over two inputs):
       // +3..+6% at 768 to 960 blocks from 4608 items on, +1..+4% at 616 and 720 blocks;
       // -2..-7% at 600 blocks, -7..-17% at 252 to 504; -3% at 960 blocks and 2880 items.
       if constexpr (D == 128) {
-        if (!stream && items >= kLoaderItems && nb_max >= kLoaderBlocks)
+        if (g.BS == 64 && !stream && items >= kLoaderItems && nb_max >= kLoaderBlocks)
           return loader(attn_loader_kernel<D, 2, RASTER, MULTI>, 2);
       }
       return SPADE_ATTN_WALK(2);
@@ -1075,18 +1058,14 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
       // blocked: 3.016 against 2.956 ms; of 720: 7.12, 6.98); at 2016 items and fewer the walk
       // is 1..29% faster.
       if constexpr (D == 128) {
-        if (!stream && items >= kLoaderItems) return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);
+        if (g.BS == 96 && !stream && items >= kLoaderItems)
+          return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);
       }
       return SPADE_ATTN_WALK(3);
     case 4: return SPADE_ATTN_WALK(4);
     case 5:
-      if constexpr (D == 64) {
-        return five(attn_pp_kernel<D, 5, RASTER, MULTI>);
-      } else {
-        if (nb_max <= kSwBlocks) return five(attn_sw_kernel<D, 5, RASTER, MULTI>);
-        if (nb_max <= kPpBlocks) return five(attn_pp_kernel<D, 5, RASTER, MULTI>);
-        return five(attn_kernel<D, 5, RASTER, MULTI, true>);
-      }
+      return run(attn_sw_kernel<D, RASTER, MULTI>, 512, FiveTileLayout<D>::BYTES,
+                 FiveTileLayout<D>::BYTES);
     case 6:
       // At d = 64 four of the loader kernel's waves (101 registers) fit a SIMD, three of the
       // walk's (157). Launches of more than 2.5 items per CU, loader against walk: 1.56, 1.85 ms
@@ -1099,7 +1078,7 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
         return SPADE_ATTN_WALK(6);
       }
     case 7:
-      // at d = 64 seven waves of up to 128 registers plus a loader leave room for two
+      // at d = 64 seven waves of 101 registers plus a loader leave room for two
       // workgroups per CU, the walk's seven of 157 for one: 3.23 against 3.47 ms (57600
       // tokens, 12 heads)
       if constexpr (D == 64)

@@ -100,18 +100,24 @@ def test_several_gpus_are_refused():
     assert r.stdout == ""
 
 
-@pytest.mark.parametrize("bt,bh,bw,d,nb,kernel", [
-    (4, 5, 8, 128, 360, "attn_sw_kernel"),     # Hunyuan's blocks: the software-pipelined kernel
-    (3, 6, 8, 128, 245, "attn_sw_kernel"),     # 144 slots, five tiles
-    (4, 5, 8, 128, 3824, "attn_sw_kernel"),    # the longest kept list its 9-chunk ring leaves room for
-    (4, 5, 8, 128, 3825, "attn_pp_kernel"),    # one more: the paired kernel's 8-chunk ring
-    (4, 5, 8, 64, 360, "attn_pp_kernel"),      # d = 64: the paired kernel
-    (4, 5, 8, 128, 7928, "attn_pp_kernel"),
-    (4, 5, 8, 128, 7929, "attn_kernel"),       # past the paired kernel's list space
-    (3, 5, 8, 128, 630, "attn_kernel"),        # 120 slots (four tiles)
+@pytest.mark.parametrize("bt,bh,bw,d,H,nb,kernel", [
+    (4, 5, 8, 128, 24, 360, "attn_sw_kernel"),     # Hunyuan's blocks: five row tiles
+    (3, 6, 8, 128, 12, 245, "attn_sw_kernel"),     # 144 slots, five tiles
+    (4, 5, 8, 128, 1, 8000, "attn_sw_kernel"),     # lists of any length
+    (4, 5, 8, 64, 24, 360, "attn_sw_kernel"),      # either head dimension
+    (3, 5, 8, 128, 40, 630, "attn_kernel"),        # 120 slots (four tiles)
+    (1, 8, 8, 128, 24, 960, "attn_loader_kernel"),  # 64 slots: 4096 items and 608 blocks on
+    (1, 8, 8, 128, 4, 960, "attn_kernel"),
+    (1, 8, 8, 128, 24, 600, "attn_kernel"),
+    (3, 4, 5, 128, 24, 960, "attn_kernel"),        # 60 slots: streamed
+    (1, 8, 8, 64, 24, 960, "attn_kernel"),
+    (3, 4, 8, 128, 24, 171, "attn_loader_kernel"),  # 96 slots: 4096 items on
+    (3, 4, 8, 128, 24, 170, "attn_kernel"),
+    (4, 6, 8, 64, 5, 128, "attn_kernel"),          # 161..192 slots, d = 64: past 640 items
+    (4, 6, 8, 64, 5, 129, "attn_loader_kernel"),
+    (4, 7, 8, 64, 1, 9, "attn_loader_kernel"),     # 193..224 slots, d = 64: always
 ])
-def test_kernel_label_follows_the_dispatch(bt, bh, bw, d, nb, kernel):
-    """The bench names the kernel the library launches: the LDS budgets of the 5-tile
-    kernels (ring + slot table + per-slot key counts + kept list <= 160 KB)."""
-    g = SimpleNamespace(bt=bt, bh=bh, bw=bw, d=d, NB=nb)
+def test_kernel_label_follows_the_dispatch(bt, bh, bw, d, H, nb, kernel):
+    """The bench names the kernel the library launches (the lines of its dispatch)."""
+    g = SimpleNamespace(B=1, H=H, bt=bt, bh=bh, bw=bw, d=d, NB=nb)
     assert bench.attn_kernel_label(g).split()[1] == kernel

@@ -33,16 +33,16 @@ def _case(name):
         "bs256_max": dict(T=8, Hs=16, Ws=12, bt=4, bh=8, bw=8, d=128, H=1),    # BS 256: 8 waves
         "one_token": dict(T=1, Hs=1, Ws=1, bt=1, bh=1, bw=1, d=64, H=2),       # NB = BS = N = 1
         "one_block": dict(T=3, Hs=5, Ws=7, bt=4, bh=8, bw=8, d=128, H=2),      # a single padded block
-        # workgroups without a loader wave (4 or 6 compute waves), ragged on every axis
+        # four and six row tiles, ragged on every axis
         "w4_ragged": dict(T=7, Hs=12, Ws=21, bt=3, bh=5, bw=8, d=128, H=2),    # BS 120
         "w4_ragged_d64": dict(T=9, Hs=11, Ws=12, bt=4, bh=5, bw=5, d=64, H=2),  # BS 100
         "w6_ragged": dict(T=7, Hs=13, Ws=23, bt=3, bh=6, bw=10, d=128, H=2),   # BS 180
-        # paired-wave kernel (5 row tiles): ragged on every axis; a 5th tile of 8 rows
+        # five row tiles: ragged on every axis; a 5th tile of 8 rows
         "pp_ragged_d64": dict(T=7, Hs=11, Ws=19, bt=4, bh=5, bw=8, d=64, H=2),  # BS 160
         "pp_bs136": dict(T=5, Hs=19, Ws=16, bt=1, bh=17, bw=8, d=128, H=2),     # BS 136
-        # the paired kernel's smallest block: a 5th tile of one row, a last chunk of one key
+        # five row tiles, the smallest block: a 5th tile of one row, a last chunk of one key
         "pp_bs129": dict(T=2, Hs=7, Ws=50, bt=1, bh=3, bw=43, d=128, H=2),      # BS 129
-        # single-member workgroups of 3 and 7 compute waves (with a loader), ragged
+        # three and seven row tiles, ragged
         "w3_ragged": dict(T=5, Hs=11, Ws=20, bt=2, bh=4, bw=9, d=128, H=2),     # BS 72
         "w7_ragged_d64": dict(T=3, Hs=21, Ws=23, bt=2, bh=10, bw=10, d=64, H=2),  # BS 200
         # d = 64 for the 6- and 8-wave workgroups
@@ -375,9 +375,8 @@ def test_attention_at_the_block_count_limit(raster):
 
 @pytest.mark.parametrize("raster", [True, False], ids=["raster", "blocked"])
 def test_attention_five_tiles_beyond_the_paired_list_space(raster):
-    """Blocks of 129..160 slots go to the paired kernel only while its LDS holds the
-    kept list beside the 8-chunk ring (d = 128: NB <= 7928); beyond, the 5-wave
-    single-member kernel takes them. NB = 8000 of 136-slot blocks: one row keeps every
+    """Blocks of 129..160 slots with lists far longer than the 512 entries that the
+    kernel stages at a time. NB = 8000 of 136-slot blocks: one row keeps every
     block, one 5000, one a single block, one none, the rest 6 random blocks; sampled
     rows against the oracle on the same lists."""
     cfg = P.small_cfg(16, 425, 160, 1, 17, 8, d=128, H=1, B=1)  # 16 x 25 x 20 blocks

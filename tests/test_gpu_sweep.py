@@ -253,7 +253,7 @@ def test_sweep_raster_multi_equals_grouped(case):
     if case == "hunyuan":
         cfg, cands, sp = workload("hunyuan_sweep"), SWEEP_CANDIDATES, 0.85
     elif case == "small_pair_b2":
-        # three 160-slot blockings (paired-wave kernel, different grids of blocks) beside a
+        # three 160-slot blockings (five row tiles, different grids of blocks) beside a
         # 120-slot one, two batch elements (the per-batch head ranking)
         cfg = P.small_cfg(6, 15, 16, 1, 1, 1, d=64, H=4, B=2)
         cands, sp = [(2, 5, 16), (4, 5, 8), (5, 4, 8), (3, 5, 8)], 0.6

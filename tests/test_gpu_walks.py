@@ -1,12 +1,12 @@
 """Kept-walk lengths of the 5-tile attention kernels, element-wise against the oracle.
 
 Blocks of 160 slots at d = 128 run the software-pipelined kernel: one barrier per
-window of four chunks, chunk c in ring slot c mod 9, the fifth row tile split over
-four waves by chunk index mod 4 and merged by log-sum-exp. Every residue of the walk
-length modulo 4 and 9, and walks shorter than one window, must give Eq. (2) on the
-given lists. The grid is ragged on every axis, so some query blocks hold fewer than
-129 real rows (the fifth tile, or more, has no rows) and some key blocks fill only
-one or two chunks.
+window of four chunks, chunk c's keys in ring slot c mod 8 and its values in slot c mod
+10, the fifth row tile split over four waves by chunk index mod 4 and merged by
+log-sum-exp. Walks over many residues modulo 4, 8 and 10, and walks shorter than one
+window, must give Eq. (2) on the given lists. The grid is ragged on every axis, so some
+query blocks hold fewer than 129 real rows (the fifth tile, or more, has no rows) and some
+key blocks fill only one or two chunks.
 """
 import numpy as np
 import pytest
