@@ -950,24 +950,29 @@ __global__ void __launch_bounds__(64 * (W + 1))
   }
 }
 
-// Whether walking a geometry's keys as one stream saves at least 3% of its chunks: the
-// look-up of chunks that span two blocks costs 2-4% (128-slot blocks whose edge blocks
-// are multiples of 32 keys: 2.67 against 2.74 ms; 120-slot blocks: 26.8 ms with the
-// stream against 28.6 without it).
-// Blocks of fewer than 32 keys keep a list from being a stream, so they count as kept.
-bool saves_chunks(const DevGeom& g) {
-  int64_t chunks = 0, keys = 0;
+// What walking a geometry's keys as one stream does: whether it saves at least 3% of the
+// chunks, and whether at least an eighth of the blocks hold fewer than 32 keys, which keep a
+// row that lists one of them from being a stream. The look-up of chunks that span two blocks
+// costs 2-4% (128-slot blocks whose edge blocks are multiples of 32 keys: 2.67 against
+// 2.74 ms; 120-slot blocks: 26.8 ms with the stream against 28.6 without it).
+struct StreamGain {
+  bool saves, many_small;
+};
+StreamGain stream_gain(const DevGeom& g) {
+  int64_t chunks = 0, keys = 0, small = 0;
   for (int k = 0; k < 8; ++k) {  // full or ragged along each axis
     const int et = (k & 1) ? g.T % g.bt : g.bt, eh = (k & 2) ? g.Hs % g.bh : g.bh;
     const int ew = (k & 4) ? g.Ws % g.bw : g.bw;
     const int64_t n = int64_t(et) * eh * ew;
+    if (n == 0) continue;
     const int64_t count = int64_t((k & 1) ? 1 : g.T / g.bt) * ((k & 2) ? 1 : g.Hs / g.bh) *
                           ((k & 4) ? 1 : g.Ws / g.bw);
     const int64_t c = (n + kChunk - 1) / kChunk;
     chunks += count * c;
     keys += count * (n < kChunk ? c * kChunk : n);
+    small += n < kChunk ? count : 0;
   }
-  return 100 * (chunks * kChunk - keys) >= 3 * chunks * kChunk;
+  return {100 * (chunks * kChunk - keys) >= 3 * chunks * kChunk, 8 * small >= g.NB};
 }
 
 // Whether a geometry's rows may be walked as a stream at all: decided by the geometry alone,
@@ -976,11 +981,15 @@ bool saves_chunks(const DevGeom& g) {
 // into chunks of its own, and a walk that does the same gives the same bits. With the 6% that
 // a ragged axis leaves to save, the stream was no faster there (960 blocks of 64 slots, 24
 // heads: 9.83 ms apart, 9.89 as a stream; 252, 12 heads: 0.380, 0.384; 392 of 96 slots, 8
-// heads: 0.902, 0.915). Nor are those of 161..224 slots at d = 64, whose large launches run
-// that kernel too.
+// heads: 0.902, 0.915). Nor are those of 65..95 slots there with many small blocks, whose
+// rows are hardly ever streams: 756 of 90 slots, 23% of them small, 24 heads 10.0 -> 9.7 ms,
+// 270 of 72 slots, 33%, 4 heads 0.271 -> 0.259; with 8% small ones the stream is 2..5% ahead.
+// Nor those of 161..224 slots at d = 64, whose large launches run the loader kernel too.
 bool may_stream(const DevGeom& g) {
-  if (g.d == 128 ? g.BS == 64 || g.BS == 96 : g.BS > 160 && g.BS <= 224) return false;
-  return saves_chunks(g);
+  const StreamGain s = stream_gain(g);
+  if (!s.saves) return false;
+  if (g.d == 128) return g.BS != 64 && g.BS != 96 && !(g.BS > 64 && g.BS < 96 && s.many_small);
+  return g.BS <= 160 || g.BS > 224;
 }
 
 // Launches `kernel` (one of the above, all with the same arguments) over the work items.
@@ -1056,9 +1065,10 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
       // Large launches of rows that are not a stream (same bits either way): with the walk
       // 96-slot blocks took 0..2% longer than with the loading wave (24 heads of 392 blocks,
       // blocked: 3.016 against 2.956 ms; of 720: 7.12, 6.98); at 2016 items and fewer the walk
-      // is 1..29% faster.
+      // is 1..29% faster. 756 90-slot blocks, 23% of them of fewer than 32 keys, at 3024 items:
+      // 1.64 ms walked, 1.67 with the loading wave.
       if constexpr (D == 128) {
-        if (g.BS == 96 && !stream && items >= kLoaderItems)
+        if (!stream && items >= kLoaderItems)
           return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);
       }
       return SPADE_ATTN_WALK(3);

@@ -20,6 +20,7 @@ import torch
 
 import bench
 import oracle.spade_oracle as O
+from paper_2608_03335_amd import spade as S
 from paper_2608_03335_amd.pipeline import block_valid_counts
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -100,24 +101,28 @@ def test_several_gpus_are_refused():
     assert r.stdout == ""
 
 
-@pytest.mark.parametrize("bt,bh,bw,d,H,nb,kernel", [
-    (4, 5, 8, 128, 24, 360, "attn_sw_kernel"),     # Hunyuan's blocks: five row tiles
-    (3, 6, 8, 128, 12, 245, "attn_sw_kernel"),     # 144 slots, five tiles
-    (4, 5, 8, 128, 1, 8000, "attn_sw_kernel"),     # lists of any length
-    (4, 5, 8, 64, 24, 360, "attn_sw_kernel"),      # either head dimension
-    (3, 5, 8, 128, 40, 630, "attn_kernel"),        # 120 slots (four tiles)
-    (1, 8, 8, 128, 24, 960, "attn_loader_kernel"),  # 64 slots: 4096 items and 608 blocks on
-    (1, 8, 8, 128, 4, 960, "attn_kernel"),
-    (1, 8, 8, 128, 24, 600, "attn_kernel"),
-    (3, 4, 5, 128, 24, 960, "attn_kernel"),        # 60 slots: streamed
-    (1, 8, 8, 64, 24, 960, "attn_kernel"),
-    (3, 4, 8, 128, 24, 171, "attn_loader_kernel"),  # 96 slots: 4096 items on
-    (3, 4, 8, 128, 24, 170, "attn_kernel"),
-    (4, 6, 8, 64, 5, 128, "attn_kernel"),          # 161..192 slots, d = 64: past 640 items
-    (4, 6, 8, 64, 5, 129, "attn_loader_kernel"),
-    (4, 7, 8, 64, 1, 9, "attn_loader_kernel"),     # 193..224 slots, d = 64: always
+@pytest.mark.parametrize("bt,bh,bw,d,H,grid,kernel", [
+    (4, 5, 8, 128, 24, (16, 45, 80), "attn_sw_kernel"),     # Hunyuan's blocks: five row tiles
+    (3, 6, 8, 128, 12, (21, 30, 52), "attn_sw_kernel"),     # 144 slots, five tiles
+    (4, 5, 8, 128, 1, (80, 100, 160), "attn_sw_kernel"),    # lists of any length
+    (4, 5, 8, 64, 24, (16, 45, 80), "attn_sw_kernel"),      # either head dimension
+    (3, 5, 8, 128, 40, (21, 45, 80), "attn_kernel"),        # 120 slots (four tiles)
+    (1, 8, 8, 128, 24, (16, 45, 80), "attn_loader_kernel"),  # 64 slots: 4096 items, 608 blocks on
+    (1, 8, 8, 128, 4, (16, 45, 80), "attn_kernel"),
+    (1, 8, 8, 128, 24, (10, 45, 80), "attn_kernel"),
+    (3, 4, 5, 128, 24, (48, 48, 25), "attn_kernel"),        # 60 slots: always walked
+    (1, 8, 8, 64, 24, (16, 45, 80), "attn_kernel"),
+    (3, 4, 8, 128, 24, (27, 36, 72), "attn_loader_kernel"),  # 96 slots: 4096 items on
+    (3, 4, 8, 128, 24, (27, 76, 8), "attn_loader_kernel"),
+    (3, 4, 8, 128, 24, (30, 68, 8), "attn_kernel"),
+    (3, 5, 6, 128, 24, (16, 45, 80), "attn_loader_kernel"),  # 90 slots, 23% of under 32 keys
+    (3, 5, 6, 128, 5, (16, 45, 80), "attn_kernel"),
+    (4, 4, 5, 128, 24, (16, 45, 80), "attn_kernel"),        # 80 slots, 8% of them: streamed
+    (4, 6, 8, 64, 5, (32, 48, 16), "attn_kernel"),          # 161..192 slots, d = 64: past 640 items
+    (4, 6, 8, 64, 5, (4, 258, 24), "attn_loader_kernel"),
+    (4, 7, 8, 64, 1, (12, 21, 8), "attn_loader_kernel"),     # 193..224 slots, d = 64: always
 ])
-def test_kernel_label_follows_the_dispatch(bt, bh, bw, d, H, nb, kernel):
+def test_kernel_label_follows_the_dispatch(bt, bh, bw, d, H, grid, kernel):
     """The bench names the kernel the library launches (the lines of its dispatch)."""
-    g = SimpleNamespace(B=1, H=H, bt=bt, bh=bh, bw=bw, d=d, NB=nb)
+    g = S.geom(1, H, d, *grid, bt, bh, bw)
     assert bench.attn_kernel_label(g).split()[1] == kernel
