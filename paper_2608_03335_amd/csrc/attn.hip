@@ -22,11 +22,13 @@
 // chunks skip the 64-register rescale; row sums use bf16 dot2 on the same packed
 // P that feeds the MFMA.
 //
-// What bounds it: the chip's power. At 1.6-1.7 GHz (2.4 when idle) the matrix pipes of a
-// dense walk are busy about 60% of the cycles; a mix of just this step's MFMAs, vector
-// work and LDS reads, without any loads from memory, ran at 1.3 PFLOP/s on the same card,
-// the walk's padded rate is 1.05-1.1. Fewer instructions and LDS bytes per MFMA, and
-// chunks without padding, are therefore what helps.
+// What bounds it: with long lists the chip's power. At 1.6-1.7 GHz (2.4 when idle) the
+// matrix pipes of a dense walk are busy about 60% of the cycles; a mix of just this step's
+// MFMAs, vector work and LDS reads, without any loads from memory, ran at 1.3 PFLOP/s on the
+// same card, the dense walk's padded rate is 1.05-1.1. Sparse lists stay 10-12% below that:
+// busy 51% at 1.88 GHz, with 27% of the wave cycles in waits and barriers (57600 tokens, 24
+// heads, a seventh of the pairs). Fewer instructions and LDS bytes per MFMA, and chunks
+// without padding, are what helped both.
 #include <climits>
 #include <mutex>
 #include <type_traits>
@@ -982,7 +984,7 @@ StreamGain stream_gain(const DevGeom& g) {
 // a ragged axis leaves to save, the stream was no faster there (960 blocks of 64 slots, 24
 // heads: 9.83 ms apart, 9.89 as a stream; 252, 12 heads: 0.380, 0.384; 392 of 96 slots, 8
 // heads: 0.902, 0.915). Nor are those of 65..95 slots there with many small blocks, whose
-// rows are hardly ever streams: 756 of 90 slots, 23% of them small, 24 heads 10.0 -> 9.7 ms,
+// rows are hardly ever streams: 756 of 90 slots, 23% of them small, 24 heads 10.5 -> 10.2 ms,
 // 270 of 72 slots, 33%, 4 heads 0.271 -> 0.259; with 8% small ones the stream is 2..5% ahead.
 // Nor those of 161..224 slots at d = 64, whose large launches run the loader kernel too.
 bool may_stream(const DevGeom& g) {
@@ -1066,7 +1068,7 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
       // 96-slot blocks took 0..2% longer than with the loading wave (24 heads of 392 blocks,
       // blocked: 3.016 against 2.956 ms; of 720: 7.12, 6.98); at 2016 items and fewer the walk
       // is 1..29% faster. 756 90-slot blocks, 23% of them of fewer than 32 keys, at 3024 items:
-      // 1.64 ms walked, 1.67 with the loading wave.
+      // 1.60 ms walked, 1.63 with the loading wave.
       if constexpr (D == 128) {
         if (!stream && items >= kLoaderItems)
           return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);

@@ -44,13 +44,14 @@ constexpr int kQsStride = D + 2;  // doubles per staged query row
 // A workgroup's item of query rows, one of three shapes (rows, waves).
 //  (12, 4): the LDS (the score rows, then the histograms or the staged query rows) lets
 //    two or more such workgroups share a CU: one contracts while another selects.
-//  (16, 8): past that a CU holds one workgroup (NB > 729 at d = 64 and 680 at d = 128, for
-//    the exact interval estimator 725 and 597), and one wave per SIMD hides nothing: here it
-//    is 16 rows, the whole matrix tile, for 8 waves, which also fetches the key summaries a
-//    quarter less often: 528 -> 374 us at 24 heads of 960 blocks (12 rows for 8 waves 445, 12
-//    for 12 409; at 600 blocks 189 with the small group, 196 with the large one). A launch
-//    that fitted one round of two small workgroups per CU pays for it: 128 -> 148 us at 8
-//    heads of 700 blocks, midpoint intervals.
+//  (16, 8): past that a CU holds one workgroup (NB > 729 at d = 64 and 680 at d = 128; for
+//    midpoint intervals, which stage no row past the item, 723 there; for the exact interval
+//    estimator 725 and 597), and one wave per SIMD hides nothing: here it is 16 rows, the
+//    whole matrix tile, for 8 waves, which also fetches the key summaries a quarter less
+//    often: 528 -> 374 us at 24 heads of 960 blocks (12 rows for 8 waves 445, 12 for 12 409;
+//    at 600 blocks 189 with the small group, 196 with the large one). Midpoint intervals at
+//    d = 128 are slower with it while two small ones fit: 143 -> 162 us at 8 heads of 720
+//    blocks, 212 -> 239 at 12, 369 -> 397 at 24.
 //  (4, 4): a launch with at most one item per CU takes as long as one item, and that is
 //    shortest with one row per wave: 35 -> 22 us at 2 heads of 360 blocks, 57 -> 42 at one
 //    of 960; with two items per CU the sixteen-row matrix tile done for four rows is felt
@@ -396,12 +397,12 @@ __global__ void __launch_bounds__(G::threads)
       // 122 -> 104 us at 24 heads of 360 blocks (where a CU has one or two workgroups in all it
       // costs 3 to 6%: 71.6 -> 74.8 at 12 heads).
       constexpr int HQ = KQ / 2;
-      double* qs = reinterpret_cast<double*>(hist_w);  // [16][kQsStride]
-      for (int e = threadIdx.x; e < 16 * D; e += kThreads) {
+      double* qs = reinterpret_cast<double*>(hist_w);  // [kRows][kQsStride]
+      for (int e = threadIdx.x; e < kRows * D; e += kThreads) {
         const int r = e / D, row = i0 + r;
         const int64_t at = int64_t(row) * D + e % D;
         qs[r * kQsStride<D> + e % D] =
-            (r < kRows && row < NB) ? (q0[at] + p.q1[bh * NB * D + at]) * 0.5 : 0.0;
+            row < NB ? (q0[at] + p.q1[bh * NB * D + at]) * 0.5 : 0.0;
       }
       __syncthreads();
       const double* const k1 = p.k1 + bh * NB * D;
@@ -416,7 +417,8 @@ __global__ void __launch_bounds__(G::threads)
         }
       };
       auto half = [&](f64x4 acc, const double2 (&x)[HQ], const double2 (&n)[HQ], int h) {
-        const double* qrow = qs + r16 * kQsStride<D> + 2 * g4 + 8 * HQ * h;
+        // tile rows past the item repeat its last one
+        const double* qrow = qs + min(r16, kRows - 1) * kQsStride<D> + 2 * g4 + 8 * HQ * h;
 #pragma unroll
         for (int kq = 0; kq < HQ; ++kq) {
           const double2 q = *reinterpret_cast<const double2*>(qrow + 8 * kq);
@@ -632,8 +634,8 @@ template <int D, int EST, class G>
 constexpr size_t group_lds(int NB) {
   constexpr int kRows = G::rows, kWaves = G::waves;
   const size_t sel = size_t(kWaves) * 256 * 8 + size_t(NB) * (4 + 1) + kRows;
-  const size_t qst = EST == kEstDsa2 ? size_t(kRows) * D * 2 * sizeof(double)
-                                     : size_t(16) * kQsStride<D> * sizeof(double);
+  const size_t rows = EST == kEstMean ? 16 : kRows;
+  const size_t qst = rows * (EST == kEstDsa2 ? 2 * D : kQsStride<D>) * sizeof(double);
   return size_t(kRows) * NB * sizeof(double) + (sel > qst ? sel : qst);
 }
 

@@ -56,7 +56,7 @@ def _both(g, Q, K, V, c, i):
 def test_noalloc_equals_workspace_call_twice_then_smaller():
     # first: 160-slot blocks (five row tiles), 3 heads x 2 batch elements, ragged grid
     big = _case(7, 11, 19, 4, 5, 8, 128, 3, 2, seed=11)
-    # second, smaller: 120-slot blocks (single-member kernel), 2 heads, d = 64
+    # second, smaller: 120-slot blocks (four row tiles), 2 heads, d = 64
     small = _case(5, 9, 13, 3, 5, 8, 64, 2, 1, seed=12)
     _say("noalloc: big")
     first = _both(*big)
