@@ -157,31 +157,32 @@ def cpu_baseline(Q, K, V, cfg, budget_s: float, call_flops: float) -> dict:
 
 
 def rows_stream(g) -> bool:
-    """Whether the library may walk the keys of 65..96-slot blocks at d = 128 as one stream:
-    chunks of 32 keys cut at block ends waste at least 3% (blocks of fewer keys not counted),
-    and fewer than an eighth of the blocks hold under 32 keys."""
+    """Whether the library may walk the keys of 65..96-slot blocks as one stream: chunks of 32
+    keys cut at block ends waste at least 3% (blocks of fewer keys not counted); at d = 128
+    also fewer than 96 slots, and fewer than an eighth of the blocks hold under 32 keys."""
     n = block_valid_counts(g)
     chunks = -(-n // 32)
     wasted = np.where(n < 32, 0, chunks * 32 - n).sum()
-    return (g.bt * g.bh * g.bw < 96 and 100 * wasted >= 3 * 32 * chunks.sum()
-            and 8 * (n < 32).sum() < n.size)
+    return 100 * wasted >= 3 * 32 * chunks.sum() and (
+        g.d == 64 or (g.bt * g.bh * g.bw < 96 and 8 * (n < 32).sum() < n.size))
 
 
-def attn_kernel_label(g) -> str:
+def attn_kernel_label(g, blocked: bool = False) -> str:
     """Which attention kernel the library launches for this blocking: blocks of 5 row tiles
     (129..160 slots) run the 8-wave walk, attn_sw_kernel; large launches of 64- and 65..96-slot
-    blocks at d = 128 whose keys are not walked as a stream and of 161..192-slot ones at
-    d = 64, and every launch of 193..224-slot ones there, the kernel with a loading wave;
-    everything else attn_kernel."""
+    blocks at d = 128 whose keys are not walked as a stream (in the blocked form the latter at
+    d = 64 too) and of 161..192-slot ones at d = 64, and every launch of 193..224-slot ones
+    there, the kernel with a loading wave; everything else attn_kernel."""
     slots, items = g.bt * g.bh * g.bw, g.B * g.H * g.NB
     tiles = -(-slots // 32)
     if tiles == 5:
         return "spade attn_sw_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
-    if g.d == 128:
-        loader = items >= 4096 and (slots == 64 and g.NB >= 608 or
-                                    tiles == 3 and not rows_stream(g))
+    if tiles == 2:
+        loader = slots == 64 and g.d == 128 and items >= 4096 and g.NB >= 608
+    elif tiles == 3:
+        loader = (g.d == 128 or blocked) and items >= 4096 and not rows_stream(g)
     else:
-        loader = tiles == 7 or (tiles == 6 and items > 640)
+        loader = g.d == 64 and (tiles == 7 or (tiles == 6 and items > 640))
     if loader:
         return "spade attn_loader_kernel (loading wave, bf16 MFMA 32x32x16)"
     return "spade attn_kernel (software-pipelined waves, bf16 MFMA 32x32x16)"
@@ -504,7 +505,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": round(attn_tflops, 2), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(attn_tflops / PEAK_BF16_TFLOPS, 4),
                      "traffic": traffic,
-                     "kernel": attn_kernel_label(g),
+                     "kernel": attn_kernel_label(g, args.layout == "blocked"),
                      "work_per_launch_tflop": round(kf / 1e12, 4)},
         "cpu_baseline": cpu,
         "stages": out_stages,

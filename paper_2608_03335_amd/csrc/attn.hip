@@ -599,8 +599,8 @@ __device__ __forceinline__ void five_tile_walk(const Item& it, const uint4* __re
       const int *__restrict__ indices, float scale_log2, __bf16 *__restrict__ ob,             \
       float *__restrict__ lse, const int *__restrict__ order,                                 \
       typename std::conditional<MULTI, MultiTable, NoTable>::type tab
-constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;  // at d = 128
-constexpr int kLoaderItems64 = 640;                      // at d = 64
+constexpr int kLoaderItems = 4096, kLoaderBlocks = 608;  // blocks of 64..96 slots
+constexpr int kLoaderItems64 = 640;                      // wider ones at d = 64
 
 template <int D, int W, bool RASTER, bool MULTI, bool STREAM>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
@@ -736,7 +736,7 @@ __device__ __forceinline__ void loader_chunk(const DevGeom& g, const char* kb, c
 
 // Single-buffered phases with a loader wave: W compute waves (32 query slots each) and one
 // more that issues all loads of the next chunk while this one is computed (two LDS
-// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the four shapes
+// buffers, whole rows XOR-swizzled over their 16-byte pieces). Kept for the shapes
 // where it beats the pipelined walk (see the dispatch). The same arithmetic in the same order
 // as a walk that is not a stream: either gives the same bits.
 template <int D, int W, bool RASTER, bool MULTI>
@@ -1068,8 +1068,10 @@ hipError_t launch_d(const DevGeom& g, const void* qb, const void* kb, const void
       // 96-slot blocks took 0..2% longer than with the loading wave (24 heads of 392 blocks,
       // blocked: 3.016 against 2.956 ms; of 720: 7.12, 6.98); at 2016 items and fewer the walk
       // is 1..29% faster. 756 90-slot blocks, 23% of them of fewer than 32 keys, at 3024 items:
-      // 1.60 ms walked, 1.63 with the loading wave.
-      if constexpr (D == 128) {
+      // 1.60 ms walked, 1.63 with the loading wave. At d = 64 the loading wave is ahead in the
+      // blocked form only: 576 96-slot blocks, 24 heads 3.85 against 3.97 ms, 8 heads 1.26, 1.31;
+      // raster 3.83, 3.78 and 1.22, 1.22, up to 8% behind on other grids.
+      if constexpr (D == 128 || !RASTER) {
         if (!stream && items >= kLoaderItems)
           return loader(attn_loader_kernel<D, 3, RASTER, MULTI>, 3);
       }

@@ -118,6 +118,7 @@ def test_several_gpus_are_refused():
     (3, 5, 6, 128, 24, (16, 45, 80), "attn_loader_kernel"),  # 90 slots, 23% of under 32 keys
     (3, 5, 6, 128, 5, (16, 45, 80), "attn_kernel"),
     (4, 4, 5, 128, 24, (16, 45, 80), "attn_kernel"),        # 80 slots, 8% of them: streamed
+    (3, 4, 8, 64, 24, (27, 76, 8), "attn_kernel"),
     (4, 6, 8, 64, 5, (32, 48, 16), "attn_kernel"),          # 161..192 slots, d = 64: past 640 items
     (4, 6, 8, 64, 5, (4, 258, 24), "attn_loader_kernel"),
     (4, 7, 8, 64, 1, (12, 21, 8), "attn_loader_kernel"),     # 193..224 slots, d = 64: always
@@ -125,4 +126,6 @@ def test_several_gpus_are_refused():
 def test_kernel_label_follows_the_dispatch(bt, bh, bw, d, H, grid, kernel):
     """The bench names the kernel the library launches (the lines of its dispatch)."""
     g = S.geom(1, H, d, *grid, bt, bh, bw)
+    if d == 64 and bt * bh * bw == 96:  # by the form of the call
+        assert bench.attn_kernel_label(g, blocked=True).split()[1] == "attn_loader_kernel"
     assert bench.attn_kernel_label(g).split()[1] == kernel

@@ -91,7 +91,7 @@ def _short_lists(H, NB, longest, seed):
 @pytest.mark.parametrize("d,grid,block,H", [
     (128, (16, 37, 64), (1, 8, 8), 13), (128, (16, 37, 64), (1, 8, 8), 6),
     (128, (16, 32, 80), (1, 8, 8), 13), (128, (9, 32, 56), (3, 4, 8), 25),
-    (128, (4, 25, 62), (3, 5, 6), 38),
+    (128, (4, 25, 62), (3, 5, 6), 38), (64, (9, 32, 56), (3, 4, 8), 25),
     (64, (8, 26, 40), (4, 6, 8), 13), (64, (6, 33, 40), (3, 7, 8), 13)], ids=str)
 def test_many_heads_equal_one(d, grid, block, H):
     print("many heads against one", d, grid, block, H, flush=True)

@@ -5,10 +5,10 @@ that saves enough chunks, as one stream in which a chunk can span blocks; lists 
 in segments (256 entries for blocks of up to 64 slots, 512 for 129..160, 1024 for the
 others); launches of more than 256 work items are ranked, by one workgroup up to 1024
 (batch, head) pairs and 24576 counts; the kernel with a loading wave takes 64-slot blocks
-at d = 128 from 4096 work items and 608 blocks on, 65..96-slot ones there that are not
-streamed from 4096 items on and 161..192-slot ones at d = 64 past 640 items. Each case
-sits on one of these edges. The tolerances are those of every attention parity test (bf16
-inputs and weights, fp32 accumulation).
+at d = 128 from 4096 work items and 608 blocks on, 65..96-slot ones that are not streamed
+from 4096 items on (at d = 64 in the blocked form only) and 161..192-slot ones at d = 64
+past 640 items. Each case sits on one of these edges. The tolerances are those of every
+attention parity test (bf16 inputs and weights, fp32 accumulation).
 """
 import numpy as np
 import pytest
@@ -128,6 +128,7 @@ def test_ranking_launches(d, H, n):
     (128, 6, (19, 32, 64), (1, 8, 8)), (128, 7, (19, 32, 64), (1, 8, 8)),
     (128, 7, (15, 40, 64), (1, 8, 8)), (128, 7, (16, 37, 64), (1, 8, 8)),
     (128, 24, (9, 32, 56), (3, 4, 8)), (128, 25, (9, 32, 56), (3, 4, 8)),
+    (64, 24, (9, 32, 56), (3, 4, 8)), (64, 25, (9, 32, 56), (3, 4, 8)),
     (128, 37, (4, 25, 62), (3, 5, 6)), (128, 38, (4, 25, 62), (3, 5, 6)),
     (64, 12, (8, 26, 40), (4, 6, 8)), (64, 13, (8, 26, 40), (4, 6, 8)),
     (64, 13, (6, 33, 40), (3, 7, 8))], ids=str)
